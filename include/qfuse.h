@@ -119,7 +119,9 @@ typedef struct {
                                that would hold fewer than epoch_fill runs is left to
                                the next pass (fewer, fuller epochs for more passes).
                                0 = default: reg_qubits (every partial epoch waits)
-                               for a plan, -1 for the plans of a mixed batch (whose
+                               for a plan, or a lower threshold where that ends
+                               passes after a few runs (entanglers that serialise
+                               the circuit); 2 for the plans of a mixed batch (whose
                                merged launches favour fewer passes); -1 = none
                                waits, 1..5 = that threshold.  Results are identical
                                up to float rounding order                              */
@@ -340,7 +342,7 @@ typedef struct {
  * checkpoint segments), and the plans' launch sequences are merged: circuits
  * of one tile shape share launches, and the shapes run on concurrent streams.
  * tuning (may be NULL) applies to every circuit's plan, with batch defaults for
- * its zero fields (epoch_fill -1, i.e. no end-of-pass epoch waits; fusion_depth
+ * its zero fields (epoch_fill 2, i.e. an end-of-pass epoch of one run waits; fusion_depth
  * 12 for circuits larger than one tile), since every pass costs a merged step;
  * mode must be 0 (fused); mem_save may be set.  Errors: QF_ERR_INVALID_ARG (NULL or empty arrays,
  * samples < 1), QF_ERR_UNSUPPORTED (mode != 0, X or Y factors in an

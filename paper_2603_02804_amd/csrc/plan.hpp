@@ -47,7 +47,7 @@ struct Tuning {
   int store = -1;        // keep checkpoints of the whole batch in the forward
   int memsave = 0;       // stored pass outputs of the active segment as bfloat16 pairs
   int uncompute = 0;     // the adjoint passes rebuild psi; no recompute (1: on)
-  int fill = 0;          // end-of-pass epochs with fewer runs wait (0: R, -1: none)
+  int fill = 0;          // end-of-pass epochs with fewer runs wait (0: R or cheaper, -1: none)
 };
 
 struct Schedule {
@@ -79,6 +79,7 @@ struct Schedule {
   int max_slots = 0;
   // per-sample op counts over all forward passes
   int64_t n_perm = 0, n_u2 = 0, n_cz = 0;
+  int64_t n_groups = 0;               // run groups (register epochs)
   int64_t n_diag_thread = 0, n_diag_amp = 0;   // diagonal items folded per thread / applied per amplitude
 };
 
