@@ -63,6 +63,8 @@ __global__ __launch_bounds__(NT, (pass_min_waves<R, BWD>())) void k_pass_multi(c
   A.coef_ps = rebase(A.coef_ps, ws);
   A.ev_sh = rebase(A.ev_sh, ws);
   A.ev_ps = rebase(A.ev_ps, ws);
+  A.tab = rebase(A.tab, ws);
+  A.tco = rebase(A.tco, ws);
   A.src0 = rebase(A.src0, ws);
   A.src1 = rebase(A.src1, ws);
   A.dst = rebase(A.dst, ws);
@@ -90,6 +92,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_multi(const SmallJob* j
       a.x = P.x;
       a.csh = rebase(a.csh, ws);
       a.cps = rebase(a.cps, ws);
+      a.dsh = rebase(a.dsh, ws);
       coef_body(a, idx);
       break;
     }
@@ -99,7 +102,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_multi(const SmallJob* j
       a.cps = rebase(a.cps, ws);
       a.esh = rebase(a.esh, ws);
       a.eps = rebase(a.eps, ws);
-      event_body(a, idx);
+      a.dsh = rebase(a.dsh, ws);
+      a.tab = rebase(a.tab, ws);
+      a.tco = rebase(a.tco, ws);
+      event_body(a, blk, (int)threadIdx.x);
       break;
     }
     case SJ_REDUCE_E: {

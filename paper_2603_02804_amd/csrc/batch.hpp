@@ -113,8 +113,8 @@ struct RecordExec {
     if (n > 0) small(j, blocks_for(n), 0);
     SmallJob e = job(SJ_EVENT, circ);
     e.u.ev = make_event_args(c, d, cp);
-    const long long ne = event_items(e.u.ev);
-    if (ne > 0) small(e, blocks_for(ne), 0);
+    const long long ne = event_blocks(e.u.ev);
+    if (ne > 0) small(e, ne, 0);
   }
   void pass(const PassLaunch& L) {
     PassJob j;
@@ -403,6 +403,8 @@ inline bool check_pass_job(const PassJob& j, const PlanCore& c, uint32_t blocks,
   ok &= in_region(A.coef_ps, 32ull * std::max<int64_t>(1, (int64_t)c.B * S.n_coef_ps), r);
   ok &= in_region(A.ev_sh, 8ull * std::max(1, S.n_ev_shared), r);
   ok &= in_region(A.ev_ps, 8ull * std::max<int64_t>(1, (int64_t)c.B * S.n_ev_ps), r);
+  ok &= in_region(A.tab, 8ull * S.tabs.size() * S.NT, r);
+  ok &= in_region(A.tco, 4ull * kTabCoefs * S.tabs.size(), r);
   ok &= (uint64_t)A.sample0 + nb <= (uint64_t)c.B;
   return ok;
 }
@@ -413,11 +415,15 @@ inline bool check_small_job(const SmallJob& j, const PlanCore& c, const Region& 
   const uint64_t coef_ps = 32ull * std::max<int64_t>(1, (int64_t)c.B * S.n_coef_ps);
   switch (j.kind) {
     case SJ_COEF:
-      return in_region(j.u.coef.csh, coef_sh, r) && in_region(j.u.coef.cps, coef_ps, r);
+      return in_region(j.u.coef.csh, coef_sh, r) && in_region(j.u.coef.cps, coef_ps, r) &&
+             in_region(j.u.coef.dsh, 8ull * kDshRow * S.n_coef_shared, r);
     case SJ_EVENT:
       return in_region(j.u.ev.csh, coef_sh, r) && in_region(j.u.ev.cps, coef_ps, r) &&
              in_region(j.u.ev.esh, 8ull * std::max(1, S.n_ev_shared), r) &&
-             in_region(j.u.ev.eps, 8ull * std::max<int64_t>(1, (int64_t)c.B * S.n_ev_ps), r);
+             in_region(j.u.ev.eps, 8ull * std::max<int64_t>(1, (int64_t)c.B * S.n_ev_ps), r) &&
+             in_region(j.u.ev.dsh, 8ull * kDshRow * S.n_coef_shared, r) &&
+             in_region(j.u.ev.tab, 8ull * S.tabs.size() * S.NT, r) &&
+             in_region(j.u.ev.tco, 4ull * kTabCoefs * S.tabs.size(), r);
     case SJ_REDUCE_E:
       return in_region(j.u.re.partE, (uint64_t)j.u.re.nb * j.u.re.parts * c.C.K * 4, r) &&
              (uint64_t)j.u.re.sample0 + j.u.re.nb <= (uint64_t)c.B;

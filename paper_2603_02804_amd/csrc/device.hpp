@@ -118,12 +118,40 @@ __device__ __forceinline__ void apply_ry(float2 (&a)[1 << R], float t, float s) 
   }
 }
 
-// RY on every register bit, bits 0..R-1 in order, straight-line code.
+// The same rotation divided by cos f: x0 - t x1 and x1 + t x0 with t = tan f, two fused
+// multiply-adds per real pair instead of three.  The factor cos f is the same for every
+// amplitude: it joins the pending factor of the thread (an epoch table entry holds the
+// product over its runs), so it costs nothing here.  t may be large: each result has
+// one rounding, relative to itself.  The pass kernels are bound by VALU issue: per epoch
+// the rotations take 128 instructions per array instead of 192, and the table entry
+// replaces about 40 (diagonal items) by a load.  16 qubits x 200 layers, 512 samples:
+// forward passes 811 -> 596 us per launch, adjoint passes 1,759 -> 1,390 us; the error of
+// the gradients against complex128 falls from 1.2e-5 to 4e-6, since the table is formed
+// in double precision.
+template <int R, int J>
+__device__ __forceinline__ void apply_rot(float2 (&a)[1 << R], float t) {
+#pragma unroll
+  for (int i = 0; i < (1 << R); ++i) {
+    if (i & (1 << J)) continue;
+    constexpr int m = 1 << J;
+    const float2 x0 = a[i], x1 = a[i | m];
+    a[i] = make_float2(fmaf(-t, x1.x, x0.x), fmaf(-t, x1.y, x0.y));
+    a[i | m] = make_float2(fmaf(t, x0.x, x1.x), fmaf(t, x0.y, x1.y));
+  }
+}
+
+// The rotations of all register bits, bits 0..R-1 in order, straight-line code.  Four
+// bits or fewer: unscaled (t = tan f), which may grow a state by 2^100 until the
+// factor is applied; five: as shears (t = tan(f/2), s = sin f), since a fifth unscaled
+// rotation could overflow.
+template <int R>
+constexpr bool kScaledRot = R <= 4;
 template <int R, int J = 0>
-__device__ __forceinline__ void apply_ry_all(float2 (&a)[1 << R], const float (&t)[R], const float (&s)[R]) {
+__device__ __forceinline__ void apply_group(float2 (&a)[1 << R], const float (&t)[R], const float (&s)[R]) {
   if constexpr (J < R) {
-    apply_ry<R, J>(a, t[J], s[J]);
-    apply_ry_all<R, J + 1>(a, t, s);
+    if constexpr (kScaledRot<R>) apply_rot<R, J>(a, t[J]);
+    else apply_ry<R, J>(a, t[J], s[J]);
+    apply_group<R, J + 1>(a, t, s);
   }
 }
 
@@ -365,10 +393,12 @@ __device__ __forceinline__ uint32_t bit_pattern(int j) {
   return j == 0 ? 0xAAAAAAAAu : j == 1 ? 0xCCCCCCCCu : j == 2 ? 0xF0F0F0F0u : j == 3 ? 0xFF00FF00u : 0xFFFF0000u;
 }
 
-// Minimum waves per SIMD the pass kernels are compiled for (bounds registers).
+// Minimum waves per SIMD the pass kernels are compiled for (bounds registers).  The
+// forward fits four (128 VGPRs; three: 11% slower at 20 qubits; five spill), the adjoint
+// holds two arrays and fits three.
 template <int R, bool BWD>
 constexpr int pass_min_waves() {
-  return R <= 4 ? 3 : 1;
+  return R <= 4 ? (BWD ? 3 : 4) : 1;
 }
 
 // Backward pass workgroups: one functional partial sum per wave, slot and Pauli
@@ -389,10 +419,20 @@ struct PassCtx {
   bool active;
   int sample, lane, wave, n_slots;
 
+  // Entry `row * NT + t` of a per-thread table: a uniform row address and a 32-bit thread
+  // offset.  The offset is made opaque so that the compiler keeps the two apart (a hoisted
+  // 64-bit per-thread base costs two registers per table, which the adjoint pass spills).
+  template <class T>
+  __device__ __forceinline__ T thread_entry(const void* tab, int row, int entry_bytes) const {
+    const char* r = reinterpret_cast<const char*>(tab) + (size_t)row * (NT * entry_bytes);
+    uint32_t off = (uint32_t)t * entry_bytes;
+    asm volatile("" : "+v"(off));
+    return *reinterpret_cast<const T*>(r + off);
+  }
   // The thread's {LDS offset, logical index} bases of a layout, read from the
   // plan's per-thread table (a vector load through the caches).
   __device__ __forceinline__ uint2 base2(int layout) const {
-    return *reinterpret_cast<const uint2*>(A.tbases + ((size_t)layout * NT + t));
+    return thread_entry<uint2>(A.tbases, layout, sizeof(ThrBase));
   }
   __device__ __forceinline__ uint32_t mem_base(int layout) const {
     return A.tbases[(size_t)layout * NT + t].mem;
@@ -404,17 +444,13 @@ struct PassCtx {
 
   // op bodies, shared by the single ops and the fused epoch op.  bf, bt: the
   // thread's LDS bases of the layouts before and after the exchange.
-  __device__ __forceinline__ void perm(float2 (&a)[NA], float2 (&l)[NA], float2& ph, int from, int to,
-                                       uint32_t bf, uint32_t bt) const {
+  // rf, rt: the layouts' register contributions.
+  __device__ __forceinline__ void perm(float2 (&a)[NA], float2 (&l)[NA], float2& ph, const RegBits<R>& rf,
+                                       const RegBits<R>& rt, uint32_t bf, uint32_t bt) const {
   // flush the pending phase (an exact identity when none is pending)
   scale_all<NA>(a, ph);
   if constexpr (BWD) scale_all<NA>(l, ph);
   ph = make_float2(1.f, 0.f);
-  const LayoutRec* F = A.layouts + from;
-  const LayoutRec* T = A.layouts + to;
-  RegBits<R> rf, rt;
-  rf.load(F->lds_reg);
-  rt.load(T->lds_reg);
   if (active) {
 #pragma unroll
     for (int jj = 0; jj < NA; ++jj) lds_at(lds, bf ^ rf(jj)) = a[jj];
@@ -435,39 +471,90 @@ struct PassCtx {
   }
   }
 
-  // RY(b) as a rotation by f = b/2: shear coefficients tan(f/2), sin f; the
-  // backward un-applies it (f -> -f)
-  __device__ __forceinline__ void ry(float2 (&a)[NA], float2 (&l)[NA], float2& ph, int bit, int ref) const {
-    // one run: the group code with identity coefficients on the other bits
-    const float* cp = run_coef(A, ref, sample);
-    const float t0 = BWD ? -cld(cp + 6) : cld(cp + 6);
-    const float s0 = BWD ? -cld(cp + 1) : cld(cp + 1);
+  // A run group outside an epoch: bit j of mask has the run with coefficient ref refs[j]
+  // (the backward un-applies it: f -> -f).  Scaled rotations are scaled right away, so
+  // that functionals and expectations see the states themselves.
+  __device__ __forceinline__ void group(float2 (&a)[NA], float2 (&l)[NA], const int (&refs)[R], int mask) const {
+    float tt[R], sn[R];
+    double nrm = 1.0;   // the squared norm of the unscaled product, from the float tangents
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      tt[j] = 0.f;
+      sn[j] = 0.f;
+      if ((mask >> j) & 1) {
+        const float* cp = run_coef(A, refs[j], sample);
+        tt[j] = BWD ? -cld(cp + 6) : cld(cp + 6);
+        sn[j] = BWD ? -cld(cp + 1) : cld(cp + 1);
+        nrm *= fma((double)tt[j], (double)tt[j], 1.0);
+      }
+    }
+    apply_group<R>(a, tt, sn);
+    if constexpr (BWD) apply_group<R>(l, tt, sn);
+    if constexpr (kScaledRot<R>) {
+      const float sc = (float)rsqrt(nrm);
+#pragma unroll
+      for (int i = 0; i < NA; ++i) {
+        a[i].x *= sc;
+        a[i].y *= sc;
+        if constexpr (BWD) {
+          l[i].x *= sc;
+          l[i].y *= sc;
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void ry(float2 (&a)[NA], float2 (&l)[NA], int bit, int ref) const {
+    int refs[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) refs[j] = ref;
+    group(a, l, refs, 1 << bit);
+  }
+  __device__ __forceinline__ void ryg(float2 (&a)[NA], float2 (&l)[NA], int first, int mask) const {
+    const RygEntry* ge = A.rygs + first;
+    int refs[R], e = 0;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      refs[j] = 0;
+      if ((mask >> j) & 1) refs[j] = cld(&ge[e++].ref);
+    }
+    group(a, l, refs, mask);
+  }
+  // An epoch's run group: its coefficients stand in the epoch table, and the scale of
+  // its shared runs in the table's pending factor; per-sample runs bring their own.
+  __device__ __forceinline__ void epoch_group(float2 (&a)[NA], float2 (&l)[NA], float2& ph, const EpochRec* E,
+                                              int tab, int ps_mask) const {
+    const float* row = A.tco + (size_t)tab * kTabCoefs;
     float tt[R], sn[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      tt[j] = (j == bit) ? t0 : 0.f;
-      sn[j] = (j == bit) ? s0 : 0.f;
+      tt[j] = cld(row + j);
+      sn[j] = kScaledRot<R> ? 0.f : cld(row + 8 + j);
     }
-    apply_ry_all<R>(a, tt, sn);
-    if constexpr (BWD) apply_ry_all<R>(l, tt, sn);
-  }
-  __device__ __forceinline__ void ryg(float2 (&a)[NA], float2 (&l)[NA], float2& ph, int first, int mask) const {
-  const RygEntry* ge = A.rygs + first;
-  float tt[R], sn[R];
-  int e = 0;
+    if (ps_mask) {
+      double nrm = 1.0;
 #pragma unroll
-  for (int j = 0; j < R; ++j) {
-    tt[j] = 0.f;
-    sn[j] = 0.f;
-    if ((mask >> j) & 1) {
-      const float* cp = run_coef(A, cld(&ge[e].ref), sample);
-      tt[j] = BWD ? -cld(cp + 6) : cld(cp + 6);
-      sn[j] = BWD ? -cld(cp + 1) : cld(cp + 1);
-      ++e;
+      for (int j = 0; j < R; ++j)
+        if ((ps_mask >> j) & 1) {
+          const float* cp = run_coef(A, cld(&E->ref[j]), sample);
+          tt[j] = cld(cp + 6);
+          sn[j] = cld(cp + 1);
+          nrm *= fma((double)tt[j], (double)tt[j], 1.0);
+        }
+      if constexpr (kScaledRot<R>) {
+        const float sc = (float)rsqrt(nrm);
+        ph.x *= sc;
+        ph.y *= sc;
+      }
     }
-  }
-  apply_ry_all<R>(a, tt, sn);
-  if constexpr (BWD) apply_ry_all<R>(l, tt, sn);
+    if constexpr (BWD) {
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        tt[j] = -tt[j];
+        sn[j] = -sn[j];
+      }
+    }
+    apply_group<R>(a, tt, sn);
+    if constexpr (BWD) apply_group<R>(l, tt, sn);
   }
 
   // x: the thread's logical base index in the current layout
@@ -531,15 +618,9 @@ struct PassCtx {
     }
   }
   // Im<lambda|P_q|psi> (P = X, Y, Z) of m register bits: wave sums into LDS
-  __device__ __forceinline__ void func(float2 (&a)[NA], float2 (&l)[NA], float2& ph, int m, int first, int) const {
+  // sl[j]: the slot of register bit j's run, or -1 when the bit holds no run of the group.
+  __device__ __forceinline__ void func(const float2 (&a)[NA], const float2 (&l)[NA], const int (&sl)[R]) const {
     if constexpr (BWD) {
-      // functionals of every register bit; entry j (register bit j) names the
-      // run's slot, or -1 when the bit holds no run of this group
-      const FuncEntry* fe = A.funcs + first;
-      // the slots of the R register bits, read as uniform scalars
-      int sl[R];
-#pragma unroll
-      for (int j = 0; j < R; ++j) sl[j] = cld(&fe[j].slot);
       // part[wave][slot][Pauli], through an LDS-typed pointer
       __attribute__((address_space(3))) float* part = (__attribute__((address_space(3))) float*)qf_pass_part;
       if constexpr (R == 4) {
@@ -715,14 +796,17 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
         const uint32_t bf = op.a == cur_idx ? cur.x : cx.base2(op.a).x;
         cur = cx.base2(op.b);
         cur_idx = op.b;
-        cx.perm(a, l, ph, op.a, op.b, bf, cur.x);
+        RegBits<R> rf, rt;
+        rf.load((A.layouts + op.a)->lds_reg);
+        rt.load((A.layouts + op.b)->lds_reg);
+        cx.perm(a, l, ph, rf, rt, bf, cur.x);
         break;
       }
       case OP_RY:
-        cx.ry(a, l, ph, op.a, op.b);
+        cx.ry(a, l, op.a, op.b);
         break;
       case OP_RYG:
-        cx.ryg(a, l, ph, op.b, op.c);
+        cx.ryg(a, l, op.b, op.c);
         break;
       case OP_DIAGT:
         cx.diagt(a, l, ph, cx.log_base(op.a, cur_idx, cur), op.b, op.c, op.d, op.e);
@@ -740,10 +824,16 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
         for (int ei = op.a; ei < op.a + op.b; ++ei) {
           const EpochRec* E = A.epochs + ei;
           const int perm_from = cld(&E->perm_from), perm_to = cld(&E->perm_to);
-          const int diag_layout = cld(&E->diag_layout);
+          const int tab = cld(&E->tab), ps_mask = cld(&E->ps_mask);
+          RegBits<R> rf, rt;
+          rf.load(E->lds_from);
+          rt.load(E->lds_to);
+          const int czg_loop = cld(&E->czg_loop), pev_loop = cld(&E->pev_loop);
           const int n_pha = cld(&E->pha_count), pha0 = cld(&E->pha_first);
           const int cza = cld(&E->cza), cza_layout = cld(&E->cza_layout);
-          const int ry_first = cld(&E->ry_a), ry_mask = cld(&E->ry_b);
+          // what the thread owes when this epoch's exchange sends its amplitudes: one
+          // table entry in place of the epoch's diagonal items and scale factors
+          const float2 owed = cx.template thread_entry<float2>(A.tab, tab, sizeof(float2));
           if constexpr (!BWD) {
             // bases before the PERM: carried from the previous epoch (the planner chains
             // the layouts; the load is a fallback), requested before those after it so
@@ -751,15 +841,16 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
             uint32_t bf = cur.x;
             if (perm_from != cur_idx) bf = cx.base2(perm_from).x;
             const uint2 nb = cx.base2(perm_to);
-            cx.perm(a, l, ph, perm_from, perm_to, bf, nb.x);
+            cx.perm(a, l, ph, rf, rt, bf, nb.x);
             cur = nb;
             cur_idx = perm_to;
-            if (diag_layout >= 0)
-              cx.diagt(a, l, ph, cx.log_base(diag_layout, cur_idx, cur), cld(&E->czg_first), cld(&E->czg_count),
-                       cld(&E->pev_first), cld(&E->pev_count));
+            ph = owed;
+            if (czg_loop | pev_loop)
+              cx.diagt(a, l, ph, cx.log_base(cld(&E->diag_layout), cur_idx, cur), cld(&E->czg_first), czg_loop,
+                       cld(&E->pev_first), pev_loop);
             for (int p = pha0; p < pha0 + n_pha; ++p) cx.phasea(a, l, ph, cld(&A.phas[p].regbit), cld(&A.phas[p].pev));
             if (cza >= 0) cx.cza(a, l, ph, cza, cx.log_base(cza_layout, cur_idx, cur));
-            cx.ryg(a, l, ph, ry_first, ry_mask);
+            cx.epoch_group(a, l, ph, E, tab, ps_mask);
           } else {
             // the tile is in layout perm_from until the PERM that ends the epoch
             if (perm_from != cur_idx) {
@@ -768,15 +859,18 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
             }
             // bases after the PERM, requested now: the epoch's work hides the load
             const uint2 nb = cx.base2(perm_to);
-            const int n_func = cld(&E->func_count);
-            if (n_func > 0) cx.func(a, l, ph, n_func, cld(&E->func_first), 0);
-            cx.ryg(a, l, ph, ry_first, ry_mask);
+            int sl[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) sl[j] = cld(&E->slot[j]);
+            cx.func(a, l, sl);
+            cx.epoch_group(a, l, ph, E, tab, ps_mask);
             if (cza >= 0) cx.cza(a, l, ph, cza, cx.log_base(cza_layout, cur_idx, cur));
             for (int p = pha0; p < pha0 + n_pha; ++p) cx.phasea(a, l, ph, cld(&A.phas[p].regbit), cld(&A.phas[p].pev));
-            if (diag_layout >= 0)
-              cx.diagt(a, l, ph, cx.log_base(diag_layout, cur_idx, cur), cld(&E->czg_first), cld(&E->czg_count),
-                       cld(&E->pev_first), cld(&E->pev_count));
-            cx.perm(a, l, ph, perm_from, perm_to, cur.x, nb.x);
+            if (czg_loop | pev_loop)
+              cx.diagt(a, l, ph, cx.log_base(cld(&E->diag_layout), cur_idx, cur), cld(&E->czg_first), czg_loop,
+                       cld(&E->pev_first), pev_loop);
+            cmul_in(ph, make_float2(owed.x, -owed.y));
+            cx.perm(a, l, ph, rf, rt, cur.x, nb.x);
             cur = nb;
             cur_idx = perm_to;
           }
@@ -786,6 +880,9 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
       case OP_EXPECT: {
         if constexpr (!BWD) {
           if (!A.do_expect) break;
+          // the pending factor may hold scale factors
+          scale_all<NA>(a, ph);
+          ph = make_float2(1.f, 0.f);
           const LayoutRec* L = A.layouts + op.a;
           const uint32_t base = cx.log_base(op.a, cur_idx, cur);
           RegBits<R> rb;
@@ -835,7 +932,12 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
         break;
       }
       case OP_FUNC:
-        cx.func(a, l, ph, op.a, op.b, op.c);
+        {
+          int sl[R];
+#pragma unroll
+          for (int j = 0; j < R; ++j) sl[j] = cld(&(A.funcs + op.b)[j].slot);
+          cx.func(a, l, sl);
+        }
         break;
       default:
         break;

@@ -71,11 +71,15 @@ struct PlanCore {
   size_t off_coef_sh = 0, off_coef_ps = 0, off_ev_sh = 0, off_ev_ps = 0;
   size_t off_ckpt = 0, off_work = 0, off_seg = 0, off_lam = 0;
   size_t off_partE = 0, off_partF = 0, off_Gr = 0, ws_bytes = 0;
+  // epoch tables: the last region of the workspace, offsets from off_ext
+  size_t off_ext = 0, ext_dsh = 0, ext_tab = 0, ext_tco = 0, ext_bytes = 0;
 };
 
 // Shape of one per-gate kernel launch: pairs per thread and threads per block.
 constexpr int kPgThreads = 256;
 constexpr int kPgPairsPerThread = 4;
+// Doubles per shared run of the epoch tables' source rows: u, v (complex) and the scale.
+constexpr int kDshRow = 6;
 // Amplitudes per thread of the Pauli-string expectation kernel.
 constexpr int kPauliAmpsPerThread = 8;
 
@@ -207,7 +211,13 @@ inline qf_status build_plan_core(const Circuit& C, int B, const Tuning& T, PlanC
                                                                              (S.general_obs ? c.pauli_blocks : c.tiles * c.waves)));
   c.off_partF = off;   off = align_up(off + sizeof(float) * std::max<int64_t>(1, int64_t(c.mb) * c.partF_seg_floats));
   c.off_Gr = off;      off = align_up(off + sizeof(float) * std::max<int64_t>(1, int64_t(c.mb) * c.n_angle));
-  c.ws_bytes = off;
+  c.off_ext = off;
+  size_t ext = 0;
+  c.ext_dsh = ext; ext = align_up(ext + sizeof(double) * kDshRow * std::max(1, S.n_coef_shared));
+  c.ext_tab = ext; ext = align_up(ext + sizeof(float) * 2 * std::max<size_t>(1, S.tabs.size() * (size_t)S.NT));
+  c.ext_tco = ext; ext = align_up(ext + sizeof(float) * kTabCoefs * std::max<size_t>(1, S.tabs.size()));
+  c.ext_bytes = ext;
+  c.ws_bytes = off + ext;
   return QF_OK;
 }
 

@@ -84,6 +84,7 @@ inline qf_status upload_plan(const PlanCore& c, DevPlan* d, std::string* msg) {
   push_table(blob, o, pauli_table(c));   // 26
   push_table(blob, o, c.C.consts);       // 27
   push_table(blob, o, thread_base_table(c.S));   // 28
+  push_table(blob, o, c.S.tabs);         // 29
   d->bytes = blob.size();
   if (hipMalloc(&d->blob, d->bytes) != hipSuccess) {
     if (msg) *msg = "hipMalloc of plan tables failed";
@@ -126,6 +127,7 @@ inline qf_status upload_plan(const PlanCore& c, DevPlan* d, std::string* msg) {
   p.pauli = (const PauliRec*)(b + o[26]);
   t.consts = (const double*)(b + o[27]);
   p.tbases = (const ThrBase*)(b + o[28]);
+  p.trecs = (const TabRec*)(b + o[29]);
   return QF_OK;
 }
 
@@ -175,6 +177,9 @@ struct qf_circuit {
 struct qf_plan {
   qf::PlanCore core;
   qf::DevPlan dev;
+  // epoch tables of qf_forward_noalloc, only where the library's array holds the rest of
+  // the plan's workspace but not them
+  char* noalloc_ext = nullptr;
   int device = 0;
   qf::Profiler prof;
 };

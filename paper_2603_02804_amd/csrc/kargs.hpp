@@ -45,6 +45,7 @@ struct PlanPtrs {
   const CzaRec* cza = nullptr;
   const PauliRec* pauli = nullptr;   // observables in the final state's bit order
   const ThrBase* tbases = nullptr;   // [layout][thread] bases (S.NT threads per layout)
+  const TabRec* trecs = nullptr;     // epoch table rows
   Tabs tabs{};
 };
 
@@ -65,6 +66,8 @@ struct KArgs {
   const float* coef_ps;
   const float* ev_sh;
   const float* ev_ps;
+  const float* tab;           // [row][NT] pending factors of the epochs (interleaved complex)
+  const float* tco;           // [row][kTabCoefs] run coefficients per register bit
   const float* src0;          // psi input, interleaved complex
   const float* src1;          // lambda input
   float* dst;
@@ -95,16 +98,24 @@ struct CoefPtrs {
   const float* cps = nullptr;
   const float* esh = nullptr;
   const float* eps = nullptr;
+  double* dsh = nullptr;      // epoch tables
+  float* tab = nullptr;
+  float* tco = nullptr;
 };
 
-inline CoefPtrs coef_ptrs(const PlanCore& c, char* ws) {
+// ext: the epoch tables' region (the workspace's last part, or memory of the plan).
+inline CoefPtrs coef_ptrs(const PlanCore& c, char* ws, char* ext) {
   CoefPtrs p;
   p.csh = at<float>(ws, c.off_coef_sh);
   p.cps = at<float>(ws, c.off_coef_ps);
   p.esh = at<float>(ws, c.off_ev_sh);
   p.eps = at<float>(ws, c.off_ev_ps);
+  p.dsh = at<double>(ext, c.ext_dsh);
+  p.tab = at<float>(ext, c.ext_tab);
+  p.tco = at<float>(ext, c.ext_tco);
   return p;
 }
+inline CoefPtrs coef_ptrs(const PlanCore& c, char* ws) { return coef_ptrs(c, ws, ws + c.off_ext); }
 
 inline KArgs make_pass_args(const PlanCore& c, const PlanPtrs& d, const CoefPtrs& cp, const PassLaunch& L) {
   const Schedule& S = c.S;
@@ -126,6 +137,8 @@ inline KArgs make_pass_args(const PlanCore& c, const PlanPtrs& d, const CoefPtrs
   A.coef_ps = cp.cps;
   A.ev_sh = cp.esh;
   A.ev_ps = cp.eps;
+  A.tab = cp.tab;
+  A.tco = cp.tco;
   A.n_ps = S.n_coef_ps;
   A.n_evps = S.n_ev_ps;
   A.src0 = L.src0;

@@ -2,6 +2,7 @@
 #include "plan.hpp"
 
 #include <algorithm>
+#include <climits>
 #include <cstring>
 #include <map>
 #include <numeric>
@@ -315,8 +316,45 @@ static void fuse_epochs(Schedule* Sp) {
   };
   auto take_diag = [&](const Op& o, EpochRec* e) {
     e->diag_layout = o.a; e->czg_first = o.b; e->czg_count = o.c; e->pev_first = o.d; e->pev_count = o.e;
+    e->czg_loop = o.f; e->pev_loop = o.g;
   };
   // consecutive epochs share one OP_EPOCH op (records are contiguous)
+  // Every exchange makes a layout of its own, so a forward epoch and its mirror share
+  // the layout of their run group, and with it the table row.
+  std::map<int, int> tab_of;
+  auto complete = [&](EpochRec* e, int layout) {
+    for (int j = 0; j < S.R; ++j) {
+      e->lds_from[j] = S.layouts[e->perm_from].lds_reg[j];
+      e->lds_to[j] = S.layouts[e->perm_to].lds_reg[j];
+    }
+    for (int j = 0; j < kMaxR; ++j)
+      e->slot[j] = e->func_count > 0 && j < S.R ? S.funcs[e->func_first + j].slot : -1;
+    TabRec t;
+    std::memset(&t, 0, sizeof(t));
+    for (int j = 0; j < kMaxR; ++j) t.ref[j] = INT32_MIN;
+    int n = 0;
+    for (int j = 0; j < S.R; ++j)
+      if ((e->ry_b >> j) & 1) {
+        const int ref = S.rygs[e->ry_a + n++].ref;
+        e->ref[j] = ref;
+        if (ref >= 0) t.ref[j] = ref;
+        else e->ps_mask |= 1 << j;
+      }
+    auto f = tab_of.find(layout);
+    if (f != tab_of.end()) {
+      e->tab = f->second;
+      return;
+    }
+    t.layout = layout;
+    t.pev_first = e->pev_first + e->pev_loop;
+    t.pev_count = e->pev_count - e->pev_loop;
+    t.czg_first = e->czg_first + e->czg_loop;
+    t.czg_count = e->czg_count - e->czg_loop;
+    t.pha_first = e->pha_first;
+    t.pha_count = e->pha_count;
+    e->tab = tab_of[layout] = (int)S.tabs.size();
+    S.tabs.push_back(t);
+  };
   auto emit = [&](const EpochRec& e) {
     if (!out.empty() && out.back().kind == OP_EPOCH && out.back().a + out.back().b == (int)S.epochs.size() &&
         (int)out.size() > cur_begin)
@@ -356,6 +394,7 @@ static void fuse_epochs(Schedule* Sp) {
         i = j;
         continue;
       }
+      complete(&e, e.perm_to);
       emit(e);
       i = j;
     }
@@ -390,6 +429,7 @@ static void fuse_epochs(Schedule* Sp) {
       e.perm_from = S.ops[j].a;
       e.perm_to = S.ops[j].b;
       ++j;
+      complete(&e, e.perm_from);
       emit(e);
       i = j;
     }
@@ -628,8 +668,10 @@ static bool build_with_fill(const Circuit& C, const Tuning& T, Schedule* Sp, std
 
     // diagonal items whose qubits are all outside the register bits: one factor per thread
     auto apply_free = [&]() {
-      std::map<int, uint32_t> groups;
-      std::vector<PhaseEv> evs;
+      // items that reach outside the tile or take per-sample angles first: the others
+      // are the same for every sample and tile (the epoch tables hold them)
+      std::map<int, uint32_t> loop_groups, groups;
+      std::vector<PhaseEv> loop_evs, evs;
       std::vector<int> keep;
       for (int id : released_list) {
         Item& it = items[id];
@@ -641,21 +683,27 @@ static bool build_with_fill(const Circuit& C, const Tuning& T, Schedule* Sp, std
         it.applied = true;
         if (it.kind == 1) {
           int lo = std::min(it.q0, it.q1), hi = std::max(it.q0, it.q1);
-          groups[hi - lo] ^= 1u << lo;
+          const bool tile_local = pos_of[lo] >= 0 && pos_of[hi] >= 0;
+          (tile_local ? groups : loop_groups)[hi - lo] ^= 1u << lo;
         } else {
-          evs.push_back(S.pev[it.ev]);
+          const PhaseEv& e = S.pev[it.ev];
+          (pos_of[it.q0] >= 0 && e.ref >= 0 ? evs : loop_evs).push_back(e);
         }
         S.n_diag_thread++;
       }
       released_list = keep;
       std::vector<CzGroup> gs;
+      for (auto& kv : loop_groups)
+        if (kv.second) gs.push_back({(uint32_t)kv.first, kv.second});
+      const int n_loop_groups = (int)gs.size(), n_loop_evs = (int)loop_evs.size();
       for (auto& kv : groups)
         if (kv.second) gs.push_back({(uint32_t)kv.first, kv.second});
+      evs.insert(evs.begin(), loop_evs.begin(), loop_evs.end());
       if (gs.empty() && evs.empty()) return;
       const int cb = (int)S.czg.size(), eb = (int)S.pev.size();
       for (auto& g : gs) S.czg.push_back(g);
       for (auto& e : evs) S.pev.push_back(e);
-      S.ops.push_back({OP_DIAGT, cur, cb, (int)gs.size(), eb, (int)evs.size(), 0, 0});
+      S.ops.push_back({OP_DIAGT, cur, cb, (int)gs.size(), eb, (int)evs.size(), n_loop_groups, n_loop_evs});
     };
     // diagonal items touching register bits: phases per register bit (PHASEA),
     // CZ signs per amplitude (one CZA for all edges)

@@ -36,7 +36,8 @@ enum OpKind : int32_t {
   OP_RY = 5,      // a=register bit, b=run coefficient ref (>=0 shared, <0 per-sample -1-idx),
                   // c=run id; backward: RY(b)^dagger on psi and lambda
   OP_DIAGT = 6,   // a=layout, b=first CZ group, c=groups, d=first phase event, e=events:
-                  // diagonal gates on thread-held qubits, folded into the pending phase
+                  // diagonal gates on thread-held qubits, folded into the pending phase; the
+                  // first f groups and g events involve other tiles or per-sample angles
   OP_CZA = 7,     // a=CzaRec, b=layout: CZ signs for edges touching register bits
   OP_PHASEA = 8,  // a=register bit, b=phase event: RZ phase on a register-held qubit
   OP_EXPECT = 9,  // a=layout: Z-string expectations of psi -> partial sums
@@ -141,17 +142,40 @@ struct PhaEntry {
 
 // The sub-ops of one epoch; -1 / 0 fields mark sub-ops that are absent.  At
 // most kEpochMaxPhaseA PHASEA sub-ops (epochs with more stay unfused; they are
-// diagonal, so their order within the epoch does not matter).
+// diagonal, so their order within the epoch does not matter).  What the kernels
+// need of other tables is repeated here, so that an epoch's scalar reads depend on
+// its index alone and not on one another.
 constexpr int kEpochMaxPhaseA = 8;
 struct EpochRec {
   int32_t perm_from, perm_to;                          // PERM (from -1: none)
+  int32_t tab;                                         // row of the epoch tables (TabRec)
+  int32_t ps_mask;                                     // register bits whose run is per-sample
+  uint32_t lds_from[kMaxR], lds_to[kMaxR];             // lds_reg of the two layouts
+  int32_t slot[kMaxR];                                 // FUNC: functional slot per register bit, or -1
+  int32_t ref[kMaxR];                                  // run group: coefficient ref per register bit (absent: 0)
   int32_t diag_layout, czg_first, czg_count, pev_first, pev_count;   // DIAGT (layout -1: none)
+  int32_t czg_loop, pev_loop;                          // the first of them that the pass kernel forms;
+                                                       // the epoch table holds the others
   int32_t pha_first, pha_count;                        // PhaEntry range
   int32_t cza, cza_layout;                             // CZA (-1: none)
   int32_t ry_kind, ry_a, ry_b;                         // run group: first RygEntry a, bit mask b (0: none)
   int32_t func_count, func_first, func_full;           // FUNC (backward; func_full unused)
-  int32_t pad;
+  int32_t pad[7];
 };
+
+// One row of the epoch tables, formed once per call by the coefficient kernels and
+// shared by all samples and tiles.  For every thread of the layout: the product of the
+// diagonal items that involve thread-held qubits and shared angles only (events
+// [pev_first, +pev_count), CZ groups [czg_first, +czg_count)) and of the scale factors
+// of the epoch's shared runs, corrected for the rounded norms of its register phases
+// (PhaEntry range).  For every register bit: the coefficients of its run.
+struct TabRec {
+  int32_t layout;
+  int32_t pev_first, pev_count, czg_first, czg_count;
+  int32_t ref[kMaxR];                                  // shared runs (INT32_MIN: none, or per-sample)
+  int32_t pha_first, pha_count;
+};
+constexpr int kTabCoefs = 16;                          // per row: t at [bit], s at [8 + bit]
 
 // Per-pass tile mapping.  Tile id bit i selects the value of the i-th non-local
 // qubit: logical bit nl_log[i], memory bit nl_in[i] before the pass and

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_coef(const CoefArgsT<Real> a)
 }
 
 __global__ __launch_bounds__(kSmallThreads) void k_event_coef(const EventArgs a) {
-  event_body(a, (long long)blockIdx.x * blockDim.x + threadIdx.x);
+  event_body(a, blockIdx.x, threadIdx.x);
 }
 
 __global__ __launch_bounds__(kSmallThreads) void k_assemble(const AssembleArgs a) {
@@ -334,6 +334,7 @@ struct GpuExec {
   const float* theta = nullptr;
   const float* x = nullptr;
   CoefPtrs cp;
+  char* ext = nullptr;   // epoch tables, if not in the workspace
   qf_status err = QF_OK;
   std::string msg;
   GpuExec(const PlanCore& pc, const DevPlan& dp, hipStream_t s) : c(pc), d(dp), st(s) {}
@@ -350,7 +351,7 @@ struct GpuExec {
   void coef(const float* th, const float* xx, char* ws) {
     theta = th;
     x = xx;
-    cp = coef_ptrs(c, ws);
+    cp = ext ? coef_ptrs(c, ws, ext) : coef_ptrs(c, ws);
     const CoefArgs a = make_coef_args(c, d.p, th, xx, cp);
     if (coef_items(a) > 0) {
       pb();
@@ -359,9 +360,9 @@ struct GpuExec {
       check("k_coef");
     }
     const EventArgs e = make_event_args(c, d.p, cp);
-    if (event_items(e) > 0) {
+    if (event_blocks(e) > 0) {
       pb();
-      hipLaunchKernelGGL(k_event_coef, dim3(blocks_for(event_items(e))), dim3(kSmallThreads), 0, st, e);
+      hipLaunchKernelGGL(k_event_coef, dim3((unsigned)event_blocks(e)), dim3(kSmallThreads), 0, st, e);
       pe(2);
       check("k_event_coef");
     }
@@ -668,9 +669,14 @@ qf_status qf_plan_create(const qf_circuit* circuit, int32_t batch, const qf_tuni
     hipGetDevice(&p->device);
     st = upload_plan(p->core, &p->dev, &msg);
   }
+  if (st == QF_OK && !p->core.per_gate && p->core.off_ext <= QF_NOALLOC_SCRATCH_BYTES &&
+      p->core.ws_bytes > QF_NOALLOC_SCRATCH_BYTES &&
+      hipMalloc((void**)&p->noalloc_ext, p->core.ext_bytes) != hipSuccess) {
+    st = QF_ERR_OOM;
+    msg = "hipMalloc of epoch tables failed";
+  }
   if (st != QF_OK) {
-    if (p->dev.blob) hipFree(p->dev.blob);
-    delete p;
+    qf_plan_destroy(p);
     return fail(st, msg);
   }
   *out = p;
@@ -680,6 +686,7 @@ qf_status qf_plan_create(const qf_circuit* circuit, int32_t batch, const qf_tuni
 qf_status qf_plan_destroy(qf_plan* p) {
   if (!p) return QF_OK;
   if (p->dev.blob) hipFree(p->dev.blob);
+  if (p->noalloc_ext) hipFree(p->noalloc_ext);
   delete p;
   return QF_OK;
 }
@@ -767,11 +774,13 @@ qf_status qf_plan_get_info(const qf_plan* p, qf_plan_info* info) {
   return QF_OK;
 }
 
-static qf_status check_call(qf_plan* p, void* ws, size_t ws_bytes) {
+// need: the workspace the call uses (default: the plan's)
+static qf_status check_call(qf_plan* p, void* ws, size_t ws_bytes, size_t need = 0) {
   if (!p) return fail(QF_ERR_INVALID_ARG, "plan is NULL");
-  if (!ws || ws_bytes < p->core.ws_bytes)
+  if (!need) need = p->core.ws_bytes;
+  if (!ws || ws_bytes < need)
     return fail(QF_ERR_WORKSPACE, "workspace of " + std::to_string(ws_bytes) + " bytes, plan needs " +
-                                      std::to_string(p->core.ws_bytes));
+                                      std::to_string(need));
   if (((uintptr_t)ws & 255) != 0) return fail(QF_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   int dev = -1;
   hipGetDevice(&dev);
@@ -800,7 +809,9 @@ qf_status qf_forward(qf_plan* p, const float* theta, const float* x, float* E, v
 
 qf_status qf_forward_noalloc(qf_plan* p, const float* theta, const float* x, float* E, void* stream) {
   if (!p) return fail(QF_ERR_INVALID_ARG, "plan is NULL");
-  if (p->core.ws_bytes > QF_NOALLOC_SCRATCH_BYTES)
+  // the epoch tables that do not fit behind the rest are the plan's own
+  const size_t need = p->noalloc_ext ? p->core.off_ext : p->core.ws_bytes;
+  if (need > QF_NOALLOC_SCRATCH_BYTES)
     return fail(QF_ERR_WORKSPACE, "qf_forward_noalloc: the plan needs a workspace of " +
                                       std::to_string(p->core.ws_bytes) + " bytes, more than the " +
                                       std::to_string((size_t)QF_NOALLOC_SCRATCH_BYTES) +
@@ -808,13 +819,14 @@ qf_status qf_forward_noalloc(qf_plan* p, const float* theta, const float* x, flo
   void* ws = nullptr;
   std::string msg;
   if (!noalloc_scratch(&ws, &msg)) return fail(QF_ERR_DEVICE, msg);
-  qf_status st = check_call(p, ws, QF_NOALLOC_SCRATCH_BYTES);
+  qf_status st = check_call(p, ws, QF_NOALLOC_SCRATCH_BYTES, need);
   if (st != QF_OK) return st;
   const PlanCore& c = p->core;
   if (c.c128) return fail(QF_ERR_INVALID_ARG, "complex128 plan: call qf_forward_c128");
   if (!E || (c.C.P > 0 && !theta) || (c.C.F > 0 && !x)) return fail(QF_ERR_INVALID_ARG, "NULL buffer");
   // no profiling events on this path: it creates nothing
   GpuExec ex(c, p->dev, (hipStream_t)stream);
+  ex.ext = p->noalloc_ext;
   st = run_forward(c, ex, theta, x, E, (char*)ws, nullptr);
   if (st != QF_OK) return fail(st, ex.msg);
   return QF_OK;

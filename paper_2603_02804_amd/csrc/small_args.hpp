@@ -10,6 +10,11 @@
 
 namespace qf {
 
+// Coefficient rows: the 2x2 matrix of a gate (per-gate paths), or the RZ RY RZ split
+// with the RY as shears or as a scaled rotation (see apply_rot in device.hpp).
+enum RunForm : int { kFormMatrix = 0, kFormShear = 1, kFormScaled = 2 };
+inline int run_form(int R) { return R <= 4 ? kFormScaled : kFormShear; }
+
 // Coefficient, reduction and gradient arguments carry the real type of the call:
 // float on the fused and per-gate paths, double on the complex128 validation path.
 template <class Real>
@@ -19,12 +24,23 @@ struct CoefArgsT {
   const Real* x;
   Real* csh;
   Real* cps;
-  int F, n_sh, n_ps, B, zyz;
+  double* dsh;     // shared runs' double rows (fused paths)
+  int F, n_sh, n_ps, B;
+  int form;        // row format: RunForm
 };
 using CoefArgs = CoefArgsT<float>;
 
 struct EventArgs {
   Tabs T;
+  const TabRec* trecs;
+  const ThrBase* tbases;
+  const PhaseEv* pev;
+  const CzGroup* czg;
+  const PhaEntry* phas;
+  const double* dsh;
+  float* tab;
+  float* tco;
+  int n_tab, NT, form;
   const float* csh;
   const float* cps;
   float* esh;
@@ -72,7 +88,7 @@ inline unsigned blocks_for(long long n, int t = kSmallThreads) {
 
 template <class Real>
 inline CoefArgsT<Real> make_coef_args_t(const PlanCore& c, const PlanPtrs& d, const Real* theta, const Real* x,
-                                        Real* csh, Real* cps) {
+                                        Real* csh, Real* cps, double* dsh = nullptr) {
   CoefArgsT<Real> a;
   a.T = d.tabs;
   a.theta = theta;
@@ -83,13 +99,15 @@ inline CoefArgsT<Real> make_coef_args_t(const PlanCore& c, const PlanPtrs& d, co
   a.n_sh = c.S.n_coef_shared;
   a.n_ps = c.S.n_coef_ps;
   a.B = c.B;
-  a.zyz = c.per_gate ? 0 : 1;
+  a.dsh = dsh;
+  a.form = c.per_gate ? kFormMatrix : run_form(c.S.R);
   return a;
 }
 
 inline CoefArgs make_coef_args(const PlanCore& c, const PlanPtrs& d, const float* theta, const float* x,
                                const CoefPtrs& cp) {
-  return make_coef_args_t<float>(c, d, theta, x, const_cast<float*>(cp.csh), const_cast<float*>(cp.cps));
+  return make_coef_args_t<float>(c, d, theta, x, const_cast<float*>(cp.csh), const_cast<float*>(cp.cps),
+                                 cp.dsh);
 }
 
 template <class Real>
@@ -98,6 +116,17 @@ inline long long coef_items(const CoefArgsT<Real>& a) { return a.n_sh + (long lo
 inline EventArgs make_event_args(const PlanCore& c, const PlanPtrs& d, const CoefPtrs& cp) {
   EventArgs a;
   a.T = d.tabs;
+  a.trecs = d.trecs;
+  a.tbases = d.tbases;
+  a.pev = d.pev;
+  a.czg = d.czg;
+  a.phas = d.phas;
+  a.dsh = cp.dsh;
+  a.tab = cp.tab;
+  a.tco = cp.tco;
+  a.n_tab = (int)c.S.tabs.size();
+  a.NT = c.S.NT;
+  a.form = run_form(c.S.R);
   a.csh = cp.csh;
   a.cps = cp.cps;
   a.esh = const_cast<float*>(cp.esh);
@@ -109,7 +138,12 @@ inline EventArgs make_event_args(const PlanCore& c, const PlanPtrs& d, const Coe
   return a;
 }
 
-inline long long event_items(const EventArgs& a) { return a.n_ev_sh + (long long)a.n_ev_ps * a.B; }
+// Phase events, then (from the next whole block) one thread per entry of the epoch tables.
+inline long long event_rows(const EventArgs& a) { return a.n_ev_sh + (long long)a.n_ev_ps * a.B; }
+inline long long event_blocks(const EventArgs& a) {
+  const long long tab = (long long)a.n_tab * a.NT;
+  return (event_rows(a) + kSmallThreads - 1) / kSmallThreads + (tab + kSmallThreads - 1) / kSmallThreads;
+}
 
 template <class Real>
 inline ReduceEArgsT<Real> make_reduce_E_args(const PlanCore& c, int nb, int sample0, int parts, const Real* partE,

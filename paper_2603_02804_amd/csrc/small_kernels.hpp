@@ -114,8 +114,17 @@ __device__ inline D2 run_matrix(const Tabs& T, const RunRec& rr, const Real* the
   return U;
 }
 
-// Run coefficients.  zyz = 1: [cos(b/2), sin(b/2), u, v, tan(b/4)] of the RZ RY RZ split;
-// zyz = 0: the 2x2 matrix row-major (one-gate runs of the per-gate baseline).
+// Least cosine of a scaled rotation: t = tan f stays below 2^25, so that four unscaled
+// rotations grow a state by less than 2^100.  The cosine moves by less than half an
+// ulp of 1, the rounding of the rotated amplitudes.
+constexpr double kMinCos = 1.0 / (1 << 25);
+
+// Run coefficients, f = b/2 of the RZ(a) RY(b) RZ(c) split.
+//   kFormShear   [cos f, sin f, u, v, tan(f/2), 0]
+//   kFormScaled  [cos f, sin f, u, v, t = tan f, 0]
+//   kFormMatrix  the 2x2 matrix row-major (one-gate runs of the per-gate paths)
+// Shared runs of the split forms also leave as doubles (dsh) u, v and the scale that
+// an unscaled rotation owes: 1/sqrt(1 + t^2) of the float t, so that no norm is lost.
 template <class Real>
 __device__ inline void coef_body(const CoefArgsT<Real>& a, long long idx) {
   if (idx >= a.n_sh + (long long)a.n_ps * a.B) return;
@@ -133,13 +142,28 @@ __device__ inline void coef_body(const CoefArgsT<Real>& a, long long idx) {
     out = a.cps + 8 * j;
   }
   const D2 U = run_matrix(a.T, a.T.runs[r], a.theta, a.x, a.F, sample);
-  if (a.zyz) {
+  if (a.form != kFormMatrix) {
     const ZYZ z = zyz_split(U);
+    // f in [0, pi/2]
+    double scale = 1.0;
+    Real t;
+    if (a.form == kFormScaled) {
+      t = (Real)(z.sb / fmax(z.cb, kMinCos));
+      scale = 1.0 / sqrt(1.0 + (double)t * (double)t);
+    } else {
+      t = (Real)(z.sb / (1.0 + z.cb));
+    }
     out[0] = (Real)z.cb; out[1] = (Real)z.sb;
     out[2] = (Real)z.ur; out[3] = (Real)z.ui;
     out[4] = (Real)z.vr; out[5] = (Real)z.vi;
-    out[6] = (Real)(z.sb / (1.0 + z.cb));   // tan(f/2) of the rotation by f = b/2, f in [0, pi/2]
+    out[6] = t;
     out[7] = 0;
+    if (idx < a.n_sh) {
+      double* d = a.dsh + kDshRow * idx;
+      d[0] = z.ur; d[1] = z.ui;
+      d[2] = z.vr; d[3] = z.vi;
+      d[4] = scale;
+    }
   } else {
     for (int i = 0; i < 4; ++i) {
       out[2 * i] = (Real)U.r[i];
@@ -148,22 +172,93 @@ __device__ inline void coef_body(const CoefArgsT<Real>& a, long long idx) {
   }
 }
 
-// Phase event coefficients w = u(prev run) * v(next run).
-__device__ inline void event_body(const EventArgs& a, long long idx) {
-  if (idx >= a.n_ev_sh + (long long)a.n_ev_ps * a.B) return;
-  int sample = 0;
-  EventRec e;
-  float* out;
-  if (idx < a.n_ev_sh) {
-    e = a.T.events[idx];
-    out = a.esh + 2 * idx;
-  } else {
-    const long long j = idx - a.n_ev_sh;
-    sample = (int)(j / a.n_ev_ps);
-    const int i = (int)(j - (long long)sample * a.n_ev_ps);
-    e = a.T.events[a.n_ev_sh + i];
-    out = a.eps + 2 * j;
+// The factor of a shared phase event, u(prev run) * v(next run) from the double rows,
+// rounded once.
+__device__ inline float2 shared_event(const double* dsh, const EventRec& e) {
+  double wr = 1.0, wi = 0.0;
+  const int ref[2] = {e.prev_ref, e.next_ref};
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if (ref[k] == INT32_MIN) continue;
+    const double* d = dsh + kDshRow * (long long)ref[k] + 2 * k;
+    const double tr = wr * d[0] - wi * d[1];
+    wi = wr * d[1] + wi * d[0];
+    wr = tr;
   }
+  return make_float2((float)wr, (float)wi);
+}
+
+// One entry of the epoch tables (TabRec): the factor that thread t of the row's layout
+// owes when the epoch's exchange sends its amplitudes, formed in double precision and
+// rounded once; and, by the first threads, the row's run coefficients.
+__device__ inline void table_body(const EventArgs& a, long long idx) {
+  if (idx >= (long long)a.n_tab * a.NT) return;
+  const int row = (int)(idx / a.NT), t = (int)(idx - (long long)row * a.NT);
+  const TabRec* r = a.trecs + row;
+  const uint32_t x = a.tbases[(size_t)r->layout * a.NT + t].log;
+  uint32_t par = 0;
+  for (int i = 0; i < r->czg_count; ++i) {
+    const CzGroup g = a.czg[r->czg_first + i];
+    par ^= x & (x >> g.shift) & g.mask;
+  }
+  double wr = __popc(par) & 1 ? -1.0 : 1.0, wi = 0.0;
+  for (int i = 0; i < r->pev_count; ++i) {
+    const PhaseEv p = a.pev[r->pev_first + i];
+    const EventRec e = a.T.events[p.ref];
+    // conjugate where the event's qubit is 1
+    const double c = (x >> p.q) & 1 ? -1.0 : 1.0;
+    const int ref[2] = {e.prev_ref, e.next_ref};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      if (ref[k] == INT32_MIN) continue;
+      const double* d = a.dsh + kDshRow * (long long)ref[k] + 2 * k;
+      const double ur = d[0], ui = c * d[1];
+      const double tr = wr * ur - wi * ui;
+      wi = wr * ui + wi * ur;
+      wr = tr;
+    }
+  }
+  double scale = 1.0;
+#pragma unroll
+  for (int j = 0; j < kMaxR; ++j)
+    if (r->ref[j] != INT32_MIN) scale *= a.dsh[kDshRow * (long long)r->ref[j] + 4];
+  // phases that the epoch applies to register-held qubits: their rounded factors' norms
+  for (int i = 0; i < r->pha_count; ++i) {
+    const PhaseEv p = a.pev[a.phas[r->pha_first + i].pev];
+    if (p.ref < 0) continue;
+    const float2 w = shared_event(a.dsh, a.T.events[p.ref]);
+    scale /= sqrt((double)w.x * w.x + (double)w.y * w.y);
+  }
+  a.tab[2 * idx] = (float)(scale * wr);
+  a.tab[2 * idx + 1] = (float)(scale * wi);
+  if (t < kTabCoefs) {
+    const int j = t & 7;
+    const bool present = j < kMaxR && r->ref[j] != INT32_MIN;
+    a.tco[(long long)row * kTabCoefs + t] = present ? a.csh[8 * (long long)r->ref[j] + (t < 8 ? 6 : 1)] : 0.f;
+  }
+}
+
+// Phase event coefficients w = u(prev run) * v(next run); the blocks after the events'
+// form the epoch tables.
+__device__ inline void event_body(const EventArgs& a, int blk, int thread) {
+  const long long rows = a.n_ev_sh + (long long)a.n_ev_ps * a.B;
+  const int ev_blocks = (int)((rows + kSmallThreads - 1) / kSmallThreads);
+  if (blk >= ev_blocks) {
+    table_body(a, (long long)(blk - ev_blocks) * kSmallThreads + thread);
+    return;
+  }
+  const long long idx = (long long)blk * kSmallThreads + thread;
+  if (idx >= rows) return;
+  if (idx < a.n_ev_sh) {
+    const float2 w = shared_event(a.dsh, a.T.events[idx]);
+    a.esh[2 * idx] = w.x;
+    a.esh[2 * idx + 1] = w.y;
+    return;
+  }
+  const long long j = idx - a.n_ev_sh;
+  const int sample = (int)(j / a.n_ev_ps);
+  const EventRec e = a.T.events[a.n_ev_sh + (int)(j - (long long)sample * a.n_ev_ps)];
+  float* out = a.eps + 2 * j;
   auto row = [&](int ref) {
     return ref >= 0 ? a.csh + 8 * (long long)ref : a.cps + 8 * ((long long)sample * a.n_ps + (-1 - ref));
   };
