@@ -78,7 +78,7 @@ __global__ __launch_bounds__(NT, (pass_min_waves<R, BWD>())) void k_pass_multi(c
 
 __global__ __launch_bounds__(kSmallThreads) void k_small_multi(const SmallJob* jobs, const int32_t* start,
                                                                int n_jobs, char* ws, const CircPtrs* ptrs) {
-  extern __shared__ double fsum[];
+  extern __shared__ double red[];
   const int b = xcd_block();
   const int j = find_job(start, n_jobs, b);
   const int kind = cld(&jobs[j].kind);
@@ -105,6 +105,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_multi(const SmallJob* j
       a.dsh = rebase(a.dsh, ws);
       a.tab = rebase(a.tab, ws);
       a.tco = rebase(a.tco, ws);
+      a.gvec = rebase(a.gvec, ws);
+      a.theta = P.theta;
       event_body(a, blk, (int)threadIdx.x);
       break;
     }
@@ -112,7 +114,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_multi(const SmallJob* j
       ReduceEArgs a = cld(&jobs[j].u.re);
       a.partE = rebase(a.partE, ws);
       a.E = P.E;
-      reduce_E_body(a, idx);
+      reduce_E_body(a, blk, (int)threadIdx.x, red);
+      break;
+    }
+    case SJ_FSUM: {
+      FsumArgs a = cld(&jobs[j].u.fs);
+      a.partF = rebase(a.partF, ws);
+      a.fsum = rebase(a.fsum, ws);
+      fsum_body(a, blk, (int)threadIdx.x, red);
       break;
     }
     case SJ_ASSEMBLE: {
@@ -120,8 +129,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_multi(const SmallJob* j
       a.theta = P.theta;
       a.x = P.x;
       a.partF = rebase(a.partF, ws);
+      a.fsum = rebase(a.fsum, ws);
+      a.gvec = rebase(a.gvec, ws);
       a.Gr = rebase(a.Gr, ws);
-      assemble_body(a, blk, fsum);
+      assemble_body(a, blk, (int)threadIdx.x, red);
       break;
     }
     case SJ_REDUCE_G: {
@@ -129,7 +140,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_multi(const SmallJob* j
       a.Gr = rebase(a.Gr, ws);
       a.dtheta = P.dtheta;
       a.dx = P.dx;
-      reduce_grads_body(a, blk, (int)threadIdx.x, fsum);
+      reduce_grads_body(a, blk, (int)threadIdx.x, red);
       break;
     }
     default:

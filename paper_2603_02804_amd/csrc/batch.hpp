@@ -89,6 +89,7 @@ struct RecordExec {
   int circ;
   CircProgram& out;
   CoefPtrs cp;
+  double* fsum = nullptr;
   RecordExec(const PlanCore& pc, const PlanPtrs& dp, int ci, CircProgram& o) : c(pc), d(dp), circ(ci), out(o) {}
   qf_status status() const { return QF_OK; }
 
@@ -112,7 +113,7 @@ struct RecordExec {
     const long long n = coef_items(j.u.coef);
     if (n > 0) small(j, blocks_for(n), 0);
     SmallJob e = job(SJ_EVENT, circ);
-    e.u.ev = make_event_args(c, d, cp);
+    e.u.ev = make_event_args(c, d, cp, nullptr);
     const long long ne = event_blocks(e.u.ev);
     if (ne > 0) small(e, ne, 0);
   }
@@ -140,18 +141,20 @@ struct RecordExec {
   void reduce_E(int nb, int sample0, const float* partE, float*) {
     SmallJob j = job(SJ_REDUCE_E, circ);
     j.u.re = make_reduce_E_args<float>(c, nb, sample0, c.tiles * c.waves, partE, nullptr);
-    small(j, blocks_for((long long)nb * c.C.K), 0);
+    small(j, reduce_E_blocks(j.u.re), reduce_shmem());
   }
   void assemble(int seg, int nb, int sample0, const float*, const float*, const float* partF, float* Gr) {
-    SmallJob j = job(SJ_ASSEMBLE, circ);
-    j.u.as = make_assemble_args(c, d, seg, nb, sample0, nullptr, nullptr, partF, Gr);
-    if (j.u.as.np == 0 || nb == 0) return;
-    small(j, (long long)nb * j.u.as.np, assemble_shmem(c));
+    SmallJob f = job(SJ_FSUM, circ), j = job(SJ_ASSEMBLE, circ);
+    f.u.fs = make_fsum_args(c, d, seg, nb, partF, fsum);
+    j.u.as = make_assemble_args(c, d, seg, nb, sample0, nullptr, nullptr, partF, fsum, cp.gvec, Gr);
+    if (assemble_blocks(j.u.as) == 0 || nb == 0) return;
+    if (fsum_blocks(f.u.fs) > 0) small(f, fsum_blocks(f.u.fs), reduce_shmem());
+    small(j, assemble_blocks(j.u.as), reduce_shmem());
   }
   void reduce_grads(int nb, int sample0, const float* Gr, float*, float*, bool accumulate) {
     SmallJob j = job(SJ_REDUCE_G, circ);
     j.u.rg = make_reduce_grads_args<float>(c, d, nb, sample0, Gr, nullptr, nullptr, accumulate);
-    if (j.u.rg.P > 0 || j.u.rg.dx_items() > 0) small(j, reduce_grads_blocks(j.u.rg), reduce_grads_shmem());
+    if (j.u.rg.P > 0 || j.u.rg.dx_items() > 0) small(j, reduce_grads_blocks(j.u.rg), reduce_shmem());
   }
 };
 
@@ -423,12 +426,19 @@ inline bool check_small_job(const SmallJob& j, const PlanCore& c, const Region& 
              in_region(j.u.ev.eps, 8ull * std::max<int64_t>(1, (int64_t)c.B * S.n_ev_ps), r) &&
              in_region(j.u.ev.dsh, 8ull * kDshRow * S.n_coef_shared, r) &&
              in_region(j.u.ev.tab, 8ull * S.tabs.size() * S.NT, r) &&
+             in_region(j.u.ev.gvec, 24ull * c.n_angle, r) &&
              in_region(j.u.ev.tco, 4ull * kTabCoefs * S.tabs.size(), r);
     case SJ_REDUCE_E:
       return in_region(j.u.re.partE, (uint64_t)j.u.re.nb * j.u.re.parts * c.C.K * 4, r) &&
              (uint64_t)j.u.re.sample0 + j.u.re.nb <= (uint64_t)c.B;
+    case SJ_FSUM: {
+      const FsumArgs& a = j.u.fs;
+      return in_region(a.partF, (uint64_t)a.nb * c.partF_seg_floats * 4, r) &&
+             in_region(a.fsum, c.ws_bytes - c.off_fsum, r) && a.chunks <= c.fsum_chunks;
+    }
     case SJ_ASSEMBLE:
-      return in_region(j.u.as.partF, (uint64_t)j.u.as.nb * c.partF_seg_floats * 4, r) &&
+      return in_region(j.u.as.fsum, c.ws_bytes - c.off_fsum, r) &&
+             in_region(j.u.as.gvec, 24ull * c.n_angle, r) && in_region(j.u.as.partF, (uint64_t)j.u.as.nb * c.partF_seg_floats * 4, r) &&
              in_region(j.u.as.Gr, (uint64_t)j.u.as.nb * c.n_angle * 4, r) &&
              (uint64_t)j.u.as.sample0 + j.u.as.nb <= (uint64_t)c.B;
     case SJ_REDUCE_G:
@@ -474,6 +484,7 @@ inline void record_programs(const std::vector<const PlanCore*>& cores, const std
     run_forward_fused(c, rf, nullptr, nullptr, nullptr, ws);
     RecordExec rb(c, ptrs[ci], (int)ci, (*bwd)[ci]);
     rb.cp = coef_ptrs(c, ws);
+    rb.fsum = at<double>(ws, c.off_fsum);
     run_backward_fused(c, rb, nullptr, nullptr, nullptr, nullptr, nullptr, ws);
   }
 }

@@ -73,6 +73,12 @@ struct PlanCore {
   size_t off_partE = 0, off_partF = 0, off_Gr = 0, ws_bytes = 0;
   // epoch tables: the last region of the workspace, offsets from off_ext
   size_t off_ext = 0, ext_dsh = 0, ext_tab = 0, ext_tco = 0, ext_bytes = 0;
+  // functional sums over the micro-batch (after the epoch tables), for the runs whose
+  // coefficients all samples share
+  std::vector<int32_t> gate_ps;       // per gate: its run is per-sample (1) or shared (0)
+  std::vector<int32_t> ps_pass, ps_begin, ps_runs;   // passes with per-sample runs, and their runs (CSR)
+  int fsum_groups = 1, fsum_chunks = 0;
+  size_t off_gvec = 0, off_fsum = 0;
 };
 
 // Shape of one per-gate kernel launch: pairs per thread and threads per block.
@@ -80,6 +86,8 @@ constexpr int kPgThreads = 256;
 constexpr int kPgPairsPerThread = 4;
 // Doubles per shared run of the epoch tables' source rows: u, v (complex) and the scale.
 constexpr int kDshRow = 6;
+// Rows of functionals that the assembly kernel adds without a chunked sum before it.
+constexpr int64_t kFsumDirect = 256;
 // Amplitudes per thread of the Pauli-string expectation kernel.
 constexpr int kPauliAmpsPerThread = 8;
 
@@ -125,6 +133,9 @@ inline qf_status build_plan_core(const Circuit& C, int B, const Tuning& T, PlanC
   }
   build_csr(C.P, th, &c.th_ref_begin, &c.th_refs);
   build_csr(C.F, in, &c.in_ref_begin, &c.in_refs);
+  c.gate_ps.assign(S.gates.size(), 1);
+  for (const RunRec& r : S.runs)
+    for (int i = 0; i < r.gate_count && r.coef >= 0 && !c.per_gate; ++i) c.gate_ps[S.run_gates[r.gate_begin + i]] = 0;
 
   const size_t SB = c.state_bytes;
   c.pauli_blocks = (int)std::max<int64_t>(1, (c.amps + int64_t(kPgThreads) * kPauliAmpsPerThread - 1) /
@@ -217,7 +228,32 @@ inline qf_status build_plan_core(const Circuit& C, int B, const Tuning& T, PlanC
   c.ext_tab = ext; ext = align_up(ext + sizeof(float) * 2 * std::max<size_t>(1, S.tabs.size() * (size_t)S.NT));
   c.ext_tco = ext; ext = align_up(ext + sizeof(float) * kTabCoefs * std::max<size_t>(1, S.tabs.size()));
   c.ext_bytes = ext;
-  c.ws_bytes = off + ext;
+  off += ext;
+  for (int p = 0; p < c.P; ++p) {
+    const size_t n0 = c.ps_runs.size();
+    for (int i = S.pass_run_begin[p]; i < S.pass_run_begin[p + 1]; ++i)
+      if (S.runs[S.pass_runs[i]].coef < 0) c.ps_runs.push_back(S.pass_runs[i]);
+    if (c.ps_runs.size() == n0) continue;
+    c.ps_pass.push_back(p);
+    c.ps_begin.push_back((int32_t)n0);
+  }
+  c.ps_begin.push_back((int32_t)c.ps_runs.size());
+  // The functionals of a pass are a matrix of (samples x tiles) rows.  Up to kFsumDirect
+  // rows the assembly adds them itself, 64 per lane, for less than the launch of another
+  // kernel (about 5 us); beyond, that kernel adds them in chunks, as many as fill the
+  // device (four workgroups per compute unit).
+  const int64_t rows = int64_t(c.mb) * c.tiles;
+  c.fsum_groups = (3 * S.max_slots + 63) / 64;
+  if (rows > kFsumDirect) {
+    const int64_t per_chunk = std::max<int64_t>(1, int64_t(c.ckpt) * c.fsum_groups);
+    c.fsum_chunks = (int)std::max<int64_t>(1, std::min<int64_t>({256, (1024 + per_chunk - 1) / per_chunk, rows / 32}));
+  }
+  int64_t seg_runs = 1;
+  for (int s = 0; s < c.n_seg; ++s)
+    seg_runs = std::max<int64_t>(seg_runs, S.pass_run_begin[c.seg_begin[s + 1]] - S.pass_run_begin[c.seg_begin[s]]);
+  c.off_gvec = off;    off = align_up(off + sizeof(double) * 3 * std::max(1, c.n_angle));
+  c.off_fsum = off;    off = align_up(off + sizeof(double) * 3 * size_t(c.fsum_chunks) * seg_runs);
+  c.ws_bytes = off;
   return QF_OK;
 }
 

@@ -70,7 +70,9 @@ inline qf_status upload_plan(const PlanCore& c, DevPlan* d, std::string* msg) {
   push_table(blob, o, c.seg_runs);       // 12
   push_table(blob, o, c.seg_run_begin);  // 13
   push_table(blob, o, c.th_ref_begin);   // 14
-  push_table(blob, o, c.th_refs);        // 15
+  std::vector<int32_t> th_refs;
+  for (int g : c.th_refs) th_refs.push_back(c.gate_ps[g] ? g : -1 - g);
+  push_table(blob, o, th_refs);          // 15
   push_table(blob, o, c.in_ref_begin);   // 16
   push_table(blob, o, c.in_refs);        // 17
   push_table(blob, o, c.S.pev);          // 18
@@ -85,6 +87,9 @@ inline qf_status upload_plan(const PlanCore& c, DevPlan* d, std::string* msg) {
   push_table(blob, o, c.C.consts);       // 27
   push_table(blob, o, thread_base_table(c.S));   // 28
   push_table(blob, o, c.S.tabs);         // 29
+  push_table(blob, o, c.ps_pass);        // 30
+  push_table(blob, o, c.ps_begin);       // 31
+  push_table(blob, o, c.ps_runs);        // 32
   d->bytes = blob.size();
   if (hipMalloc(&d->blob, d->bytes) != hipSuccess) {
     if (msg) *msg = "hipMalloc of plan tables failed";
@@ -121,6 +126,9 @@ inline qf_status upload_plan(const PlanCore& c, DevPlan* d, std::string* msg) {
   t.events = (const EventRec*)(b + o[20]);
   t.pass_run_begin = (const int32_t*)(b + o[21]);
   t.pass_runs = (const int32_t*)(b + o[22]);
+  t.ps_pass = (const int32_t*)(b + o[30]);
+  t.ps_begin = (const int32_t*)(b + o[31]);
+  t.ps_runs = (const int32_t*)(b + o[32]);
   p.rygs = (const RygEntry*)(b + o[23]);
   p.epochs = (const EpochRec*)(b + o[24]);
   p.phas = (const PhaEntry*)(b + o[25]);

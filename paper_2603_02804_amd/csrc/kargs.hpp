@@ -23,11 +23,14 @@ struct Tabs {
   const int32_t* seg_runs;
   const int32_t* seg_run_begin;
   const int32_t* th_ref_begin;
-  const int32_t* th_refs;
+  const int32_t* th_refs;       // gate g of a per-sample run, or -1 - g of a shared one
   const int32_t* in_ref_begin;
   const int32_t* in_refs;
   const int32_t* pass_run_begin;
   const int32_t* pass_runs;
+  const int32_t* ps_pass;       // passes with per-sample runs, and those runs per entry
+  const int32_t* ps_begin;
+  const int32_t* ps_runs;
   const double* consts;         // fixed angles of internal gates (lowered CNOT)
 };
 
@@ -101,6 +104,7 @@ struct CoefPtrs {
   double* dsh = nullptr;      // epoch tables
   float* tab = nullptr;
   float* tco = nullptr;
+  double* gvec = nullptr;     // per gate of a shared run: its generator at the run's cut
 };
 
 // ext: the epoch tables' region (the workspace's last part, or memory of the plan).
@@ -113,6 +117,7 @@ inline CoefPtrs coef_ptrs(const PlanCore& c, char* ws, char* ext) {
   p.dsh = at<double>(ext, c.ext_dsh);
   p.tab = at<float>(ext, c.ext_tab);
   p.tco = at<float>(ext, c.ext_tco);
+  p.gvec = at<double>(ws, c.off_gvec);
   return p;
 }
 inline CoefPtrs coef_ptrs(const PlanCore& c, char* ws) { return coef_ptrs(c, ws, ws + c.off_ext); }

@@ -911,6 +911,7 @@ int qfc_batch_run(const qf_circuit_desc* const* descs, const int32_t* samples, i
           const int c = j.circ;
           switch (j.kind) {
             case SJ_COEF: e.coef(theta[c], x[c], base + off[c]); break;
+            case SJ_FSUM: break;    // the emulated assembly adds the functionals itself
             case SJ_EVENT: break;   // the emulated coefficient step also fills the phase events
             case SJ_REDUCE_E: e.reduce_E(j.u.re.nb, j.u.re.sample0, rb(j.u.re.partE), E[c]); break;
             case SJ_ASSEMBLE:

@@ -14,6 +14,7 @@
 //                       registers; write lambda once.
 //   k_coef              merged 2x2 matrix of every run, u(phi) = cos(phi/2) I -
 //                       i sin(phi/2) P (Sec. 3.3), multiplied in gate order.
+//   k_fsum              functionals added over samples and tiles, in chunks.
 //   k_assemble          per-gate gradients of a run from its functionals:
 //                       dL/dtheta_g = Re<lambda_g|du_g|psi_{g-1}> = 1/2 Im<lambda|G_g|psi>
 //                       with G_g = K_g P_g K_g^dagger, K_g = later gates of the run.
@@ -54,9 +55,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_event_coef(const EventArgs a)
   event_body(a, blockIdx.x, threadIdx.x);
 }
 
+__global__ __launch_bounds__(kSmallThreads) void k_fsum(const FsumArgs a) {
+  __shared__ double red[kSmallThreads];
+  fsum_body(a, blockIdx.x, threadIdx.x, red);
+}
+
 __global__ __launch_bounds__(kSmallThreads) void k_assemble(const AssembleArgs a) {
-  extern __shared__ double fsum[];
-  assemble_body(a, blockIdx.x, fsum);
+  __shared__ double red[kSmallThreads];
+  assemble_body(a, blockIdx.x, threadIdx.x, red);
 }
 
 template <class Real>
@@ -67,7 +73,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_reduce_grads(const ReduceGArg
 
 template <class Real>
 __global__ __launch_bounds__(kSmallThreads) void k_reduce_E(const ReduceEArgsT<Real> a) {
-  reduce_E_body(a, (long long)blockIdx.x * blockDim.x + threadIdx.x);
+  __shared__ double red[kSmallThreads];
+  reduce_E_body(a, blockIdx.x, threadIdx.x, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -335,6 +342,8 @@ struct GpuExec {
   const float* x = nullptr;
   CoefPtrs cp;
   char* ext = nullptr;   // epoch tables, if not in the workspace
+  bool forward_only = false;
+  double* fsum = nullptr;
   qf_status err = QF_OK;
   std::string msg;
   GpuExec(const PlanCore& pc, const DevPlan& dp, hipStream_t s) : c(pc), d(dp), st(s) {}
@@ -352,6 +361,7 @@ struct GpuExec {
     theta = th;
     x = xx;
     cp = ext ? coef_ptrs(c, ws, ext) : coef_ptrs(c, ws);
+    if (forward_only) cp.gvec = nullptr;
     const CoefArgs a = make_coef_args(c, d.p, th, xx, cp);
     if (coef_items(a) > 0) {
       pb();
@@ -359,7 +369,7 @@ struct GpuExec {
       pe(2);
       check("k_coef");
     }
-    const EventArgs e = make_event_args(c, d.p, cp);
+    const EventArgs e = make_event_args(c, d.p, cp, th);
     if (event_blocks(e) > 0) {
       pb();
       hipLaunchKernelGGL(k_event_coef, dim3((unsigned)event_blocks(e)), dim3(kSmallThreads), 0, st, e);
@@ -385,16 +395,23 @@ struct GpuExec {
   void reduce_E(int nb, int sample0, const float* partE, float* E) {
     const ReduceEArgs a = make_reduce_E_args<float>(c, nb, sample0, c.tiles * c.waves, partE, E);
     pb();
-    hipLaunchKernelGGL(k_reduce_E<float>, dim3(blocks_for((long long)nb * c.C.K)), dim3(kSmallThreads), 0, st, a);
+    hipLaunchKernelGGL(k_reduce_E<float>, dim3((unsigned)reduce_E_blocks(a)), dim3(kSmallThreads), 0, st, a);
     pe(2);
     check("k_reduce_E");
   }
 
   void assemble(int seg, int nb, int sample0, const float* th, const float* xx, const float* partF, float* Gr) {
-    const AssembleArgs a = make_assemble_args(c, d.p, seg, nb, sample0, th, xx, partF, Gr);
-    if (a.np == 0 || nb == 0) return;
+    const FsumArgs f = make_fsum_args(c, d.p, seg, nb, partF, fsum);
+    const AssembleArgs a = make_assemble_args(c, d.p, seg, nb, sample0, th, xx, partF, fsum, cp.gvec, Gr);
+    if (assemble_blocks(a) == 0 || nb == 0) return;
+    if (fsum_blocks(f) > 0) {
+      pb();
+      hipLaunchKernelGGL(k_fsum, dim3((unsigned)fsum_blocks(f)), dim3(kSmallThreads), 0, st, f);
+      pe(2);
+      check("k_fsum");
+    }
     pb();
-    hipLaunchKernelGGL(k_assemble, dim3((unsigned)(nb * a.np)), dim3(kSmallThreads), assemble_shmem(c), st, a);
+    hipLaunchKernelGGL(k_assemble, dim3((unsigned)assemble_blocks(a)), dim3(kSmallThreads), 0, st, a);
     pe(2);
     check("k_assemble");
   }
@@ -467,7 +484,7 @@ struct GpuExec {
   void pauli_reduce_E(int nb, int sample0, const Real* partE, Real* E) {
     const ReduceEArgsT<Real> a = make_reduce_E_args<Real>(c, nb, sample0, c.pauli_blocks, partE, E);
     pb();
-    hipLaunchKernelGGL(k_reduce_E<Real>, dim3(blocks_for((long long)nb * c.C.K)), dim3(kSmallThreads), 0, st, a);
+    hipLaunchKernelGGL(k_reduce_E<Real>, dim3((unsigned)reduce_E_blocks(a)), dim3(kSmallThreads), 0, st, a);
     pe(2);
     check("k_reduce_E");
   }
@@ -649,16 +666,16 @@ qf_status qf_plan_create(const qf_circuit* circuit, int32_t batch, const qf_tuni
   }
   if (st == QF_OK && !p->core.per_gate) {
     // LDS of a workgroup: the pass kernels' static tile plus the adjoint pass's
-    // per-wave functional sums (they grow with the runs fused into one pass),
-    // and the assembly kernel's per-run sums; a plan that would exceed the
-    // device limit is refused here rather than failing at launch
+    // per-wave functional sums (they grow with the runs fused into one pass); a plan
+    // that would exceed the device limit is refused here rather than failing at
+    // launch (as are passes whose summed functionals alone would exceed it)
     int dev = 0, lim = 0;
     hipGetDevice(&dev);
     if (hipDeviceGetAttribute(&lim, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || lim <= 0)
       lim = 64 << 10;
     const PlanCore& c = p->core;
     const size_t tile = sizeof(float2) * ((size_t)1 << c.S.R) * c.S.NT;
-    const size_t need = std::max(tile + pass_shmem(c, true), assemble_shmem(c));
+    const size_t need = std::max(tile + pass_shmem(c, true), sizeof(double) * 3 * std::max(1, c.S.max_slots));
     if (need > (size_t)lim) {
       st = QF_ERR_UNSUPPORTED;
       msg = "a pass needs " + std::to_string(need) + " bytes of LDS per workgroup, the device allows " +
@@ -670,7 +687,7 @@ qf_status qf_plan_create(const qf_circuit* circuit, int32_t batch, const qf_tuni
     st = upload_plan(p->core, &p->dev, &msg);
   }
   if (st == QF_OK && !p->core.per_gate && p->core.off_ext <= QF_NOALLOC_SCRATCH_BYTES &&
-      p->core.ws_bytes > QF_NOALLOC_SCRATCH_BYTES &&
+      p->core.off_ext + p->core.ext_bytes > QF_NOALLOC_SCRATCH_BYTES &&
       hipMalloc((void**)&p->noalloc_ext, p->core.ext_bytes) != hipSuccess) {
     st = QF_ERR_OOM;
     msg = "hipMalloc of epoch tables failed";
@@ -810,7 +827,8 @@ qf_status qf_forward(qf_plan* p, const float* theta, const float* x, float* E, v
 qf_status qf_forward_noalloc(qf_plan* p, const float* theta, const float* x, float* E, void* stream) {
   if (!p) return fail(QF_ERR_INVALID_ARG, "plan is NULL");
   // the epoch tables that do not fit behind the rest are the plan's own
-  const size_t need = p->noalloc_ext ? p->core.off_ext : p->core.ws_bytes;
+  const PlanCore& c = p->core;
+  const size_t need = c.per_gate ? c.ws_bytes : c.off_ext + (p->noalloc_ext ? 0 : c.ext_bytes);
   if (need > QF_NOALLOC_SCRATCH_BYTES)
     return fail(QF_ERR_WORKSPACE, "qf_forward_noalloc: the plan needs a workspace of " +
                                       std::to_string(p->core.ws_bytes) + " bytes, more than the " +
@@ -821,12 +839,12 @@ qf_status qf_forward_noalloc(qf_plan* p, const float* theta, const float* x, flo
   if (!noalloc_scratch(&ws, &msg)) return fail(QF_ERR_DEVICE, msg);
   qf_status st = check_call(p, ws, QF_NOALLOC_SCRATCH_BYTES, need);
   if (st != QF_OK) return st;
-  const PlanCore& c = p->core;
   if (c.c128) return fail(QF_ERR_INVALID_ARG, "complex128 plan: call qf_forward_c128");
   if (!E || (c.C.P > 0 && !theta) || (c.C.F > 0 && !x)) return fail(QF_ERR_INVALID_ARG, "NULL buffer");
   // no profiling events on this path: it creates nothing
   GpuExec ex(c, p->dev, (hipStream_t)stream);
   ex.ext = p->noalloc_ext;
+  ex.forward_only = true;
   st = run_forward(c, ex, theta, x, E, (char*)ws, nullptr);
   if (st != QF_OK) return fail(st, ex.msg);
   return QF_OK;
@@ -845,6 +863,7 @@ qf_status qf_backward_psi0(qf_plan* p, const float* theta, const float* x, const
   ex.theta = theta;
   ex.x = x;
   ex.cp = coef_ptrs(c, (char*)ws);
+  ex.fsum = at<double>((char*)ws, c.off_fsum);
   st = run_backward(c, ex, theta, x, dE, dtheta, dx, (char*)ws, psi0);
   if (st != QF_OK) return fail(st, ex.msg);
   return QF_OK;

@@ -40,7 +40,9 @@ struct EventArgs {
   const double* dsh;
   float* tab;
   float* tco;
-  int n_tab, NT, form;
+  double* gvec;    // or null: no backward follows
+  const float* theta;
+  int n_tab, NT, form, n_sh;
   const float* csh;
   const float* cps;
   float* esh;
@@ -53,16 +55,30 @@ struct ReduceEArgsT {
   const Real* partE;
   Real* E;
   int nb, sample0, parts, K;
+  int wide;        // a workgroup per sample instead of a thread per sum
 };
 using ReduceEArgs = ReduceEArgsT<float>;
+
+// Column sums of the functionals of passes [p0, p0 + np) in chunks of their rows.
+struct FsumArgs {
+  Tabs T;
+  const float* partF;
+  double* fsum;
+  int p0, np, nb, tiles, groups, chunks;
+};
 
 struct AssembleArgs {
   Tabs T;
   const float* theta;
   const float* x;
   const float* partF;
+  const double* fsum;
+  const double* gvec;
   float* Gr;
   int p0, np, nb, sample0, tiles, n_angle, F;
+  int groups;      // workgroups per pass for the shared runs (kAssembleRuns each)
+  int chunks;      // partial sums of fsum, 0: the rows of partF
+  int ps0, nps;    // entries of T.ps_pass in the segment
 };
 
 template <class Real>
@@ -113,7 +129,7 @@ inline CoefArgs make_coef_args(const PlanCore& c, const PlanPtrs& d, const float
 template <class Real>
 inline long long coef_items(const CoefArgsT<Real>& a) { return a.n_sh + (long long)a.n_ps * a.B; }
 
-inline EventArgs make_event_args(const PlanCore& c, const PlanPtrs& d, const CoefPtrs& cp) {
+inline EventArgs make_event_args(const PlanCore& c, const PlanPtrs& d, const CoefPtrs& cp, const float* theta) {
   EventArgs a;
   a.T = d.tabs;
   a.trecs = d.trecs;
@@ -127,6 +143,9 @@ inline EventArgs make_event_args(const PlanCore& c, const PlanPtrs& d, const Coe
   a.n_tab = (int)c.S.tabs.size();
   a.NT = c.S.NT;
   a.form = run_form(c.S.R);
+  a.gvec = cp.gvec;
+  a.theta = theta;
+  a.n_sh = c.S.n_coef_shared;
   a.csh = cp.csh;
   a.cps = cp.cps;
   a.esh = const_cast<float*>(cp.esh);
@@ -138,11 +157,13 @@ inline EventArgs make_event_args(const PlanCore& c, const PlanPtrs& d, const Coe
   return a;
 }
 
-// Phase events, then (from the next whole block) one thread per entry of the epoch tables.
+// Phase events, then (each from the next whole block) one thread per entry of the epoch
+// tables and one per shared run, for its gates' generators.
 inline long long event_rows(const EventArgs& a) { return a.n_ev_sh + (long long)a.n_ev_ps * a.B; }
 inline long long event_blocks(const EventArgs& a) {
   const long long tab = (long long)a.n_tab * a.NT;
-  return (event_rows(a) + kSmallThreads - 1) / kSmallThreads + (tab + kSmallThreads - 1) / kSmallThreads;
+  return (event_rows(a) + kSmallThreads - 1) / kSmallThreads + (tab + kSmallThreads - 1) / kSmallThreads +
+         (a.gvec ? (a.n_sh + kSmallThreads - 1) / kSmallThreads : 0);
 }
 
 template <class Real>
@@ -155,11 +176,37 @@ inline ReduceEArgsT<Real> make_reduce_E_args(const PlanCore& c, int nb, int samp
   a.sample0 = sample0;
   a.parts = parts;
   a.K = c.C.K;
+  // few partial sums: a thread each keeps many samples in one workgroup (65,536 samples of
+  // 9 qubits); many: 1,024 of a 20-qubit sample took 305 us as one serial chain per thread
+  a.wide = parts > 16 ? 1 : 0;
   return a;
 }
+template <class Real>
+inline long long reduce_E_blocks(const ReduceEArgsT<Real>& a) {
+  return a.wide ? a.nb : ((long long)a.nb * a.K + kSmallThreads - 1) / kSmallThreads;
+}
+
+inline FsumArgs make_fsum_args(const PlanCore& c, const PlanPtrs& d, int seg, int nb, const float* partF,
+                               double* fsum) {
+  FsumArgs a;
+  a.T = d.tabs;
+  a.partF = partF;
+  a.fsum = fsum;
+  a.p0 = c.seg_begin[seg];
+  a.np = c.seg_begin[seg + 1] - a.p0;
+  a.nb = nb;
+  a.tiles = c.tiles;
+  a.groups = c.fsum_groups;
+  a.chunks = c.fsum_chunks;
+  return a;
+}
+inline long long fsum_blocks(const FsumArgs& a) { return (long long)a.np * a.groups * a.chunks; }
+
+constexpr int kAssembleRuns = 21;   // runs per workgroup: 63 columns of functionals
 
 inline AssembleArgs make_assemble_args(const PlanCore& c, const PlanPtrs& d, int seg, int nb, int sample0,
-                                       const float* theta, const float* x, const float* partF, float* Gr) {
+                                       const float* theta, const float* x, const float* partF, const double* fsum,
+                                       const double* gvec, float* Gr) {
   AssembleArgs a;
   a.T = d.tabs;
   a.theta = theta;
@@ -173,10 +220,18 @@ inline AssembleArgs make_assemble_args(const PlanCore& c, const PlanPtrs& d, int
   a.tiles = c.tiles;
   a.n_angle = c.n_angle;
   a.F = c.C.F;
+  a.fsum = fsum;
+  a.gvec = gvec;
+  a.groups = (c.S.max_slots + kAssembleRuns - 1) / kAssembleRuns;
+  a.chunks = c.fsum_chunks;
+  const auto lo = std::lower_bound(c.ps_pass.begin(), c.ps_pass.end(), a.p0);
+  a.ps0 = (int)(lo - c.ps_pass.begin());
+  a.nps = (int)(std::lower_bound(lo, c.ps_pass.end(), a.p0 + a.np) - lo);
   return a;
 }
-
-inline size_t assemble_shmem(const PlanCore& c) { return sizeof(double) * 3 * std::max(1, c.S.max_slots); }
+inline long long assemble_blocks(const AssembleArgs& a) {
+  return (long long)a.np * a.groups + (long long)a.nb * a.nps;
+}
 
 template <class Real>
 inline ReduceGArgsT<Real> make_reduce_grads_args(const PlanCore& c, const PlanPtrs& d, int nb, int sample0,
@@ -196,6 +251,9 @@ inline ReduceGArgsT<Real> make_reduce_grads_args(const PlanCore& c, const PlanPt
   // lanes per angle when there are few
   int cols = 1;
   while (cols < 64 && cols < a.P) cols *= 2;
+  // per-sample runs are added over the samples here: at most 64 per lane if the block allows
+  if (!c.ps_runs.empty() || c.per_gate)
+    while (cols > 1 && (long long)nb * cols > 64ll * kSmallThreads) cols /= 2;
   a.cols = cols;
   a.th_blocks = (a.P + cols - 1) / cols;
   return a;
@@ -208,7 +266,8 @@ inline long long reduce_grads_blocks(const ReduceGArgsT<Real>& a) {
   const long long nx = a.dx_items();
   return (long long)a.th_blocks + (nx + kSmallThreads - 1) / kSmallThreads;
 }
-inline size_t reduce_grads_shmem() { return sizeof(double) * kSmallThreads; }
+// LDS of the reduction kernels: one double per thread.
+inline size_t reduce_shmem() { return sizeof(double) * kSmallThreads; }
 
 // ---------------------------------------------------------------- mixed batches
 // Caller buffers of one circuit of a mixed batch, refreshed on every call.
@@ -230,7 +289,8 @@ struct PassJob {
   int32_t pass;       // pass index in the circuit's plan (host checks only)
 };
 
-enum SmallKind : int32_t { SJ_COEF = 0, SJ_EVENT = 1, SJ_REDUCE_E = 2, SJ_ASSEMBLE = 3, SJ_REDUCE_G = 4 };
+enum SmallKind : int32_t { SJ_COEF = 0, SJ_EVENT = 1, SJ_REDUCE_E = 2, SJ_ASSEMBLE = 3, SJ_REDUCE_G = 4,
+                           SJ_FSUM = 5 };
 
 // A small-kernel launch of one circuit inside a merged launch: same address
 // convention; theta, x, E, dtheta and dx come from CircPtrs.
@@ -242,6 +302,7 @@ struct SmallJob {
     EventArgs ev;
     ReduceEArgs re;
     AssembleArgs as;
+    FsumArgs fs;
     ReduceGArgs rg;
   } u;
 };
