@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_multi(const SmallJob* j
       a.tco = rebase(a.tco, ws);
       a.gvec = rebase(a.gvec, ws);
       a.theta = P.theta;
-      event_body(a, blk, (int)threadIdx.x);
+      event_body(a, blk, (int)threadIdx.x, red);
       break;
     }
     case SJ_REDUCE_E: {

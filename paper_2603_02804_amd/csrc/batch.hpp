@@ -115,7 +115,7 @@ struct RecordExec {
     SmallJob e = job(SJ_EVENT, circ);
     e.u.ev = make_event_args(c, d, cp, nullptr);
     const long long ne = event_blocks(e.u.ev);
-    if (ne > 0) small(e, ne, 0);
+    if (ne > 0) small(e, ne, reduce_shmem());
   }
   void pass(const PassLaunch& L) {
     PassJob j;

@@ -419,20 +419,29 @@ struct PassCtx {
   bool active;
   int sample, lane, wave, n_slots;
 
-  // Entry `row * NT + t` of a per-thread table: a uniform row address and a 32-bit thread
-  // offset.  The offset is made opaque so that the compiler keeps the two apart (a hoisted
-  // 64-bit per-thread base costs two registers per table, which the adjoint pass spills).
+  // Entry `row * NT + t` of a per-thread table: the wave's uniform address and the lane's
+  // 32-bit offset.  The lane id is made opaque, so that no register carries a thread
+  // offset or a 64-bit address through the epoch loop (the adjoint pass would spill them).
+  __device__ __forceinline__ uint32_t lane_id() const {
+    uint32_t id = (uint32_t)lane;
+    asm volatile("" : "+v"(id));
+    return id;
+  }
   template <class T>
-  __device__ __forceinline__ T thread_entry(const void* tab, int row, int entry_bytes) const {
-    const char* r = reinterpret_cast<const char*>(tab) + (size_t)row * (NT * entry_bytes);
-    uint32_t off = (uint32_t)t * entry_bytes;
-    asm volatile("" : "+v"(off));
-    return *reinterpret_cast<const T*>(r + off);
+  __device__ __forceinline__ T thread_entry(const void* tab, int row, int entry_bytes, uint32_t id) const {
+    const char* r = reinterpret_cast<const char*>(tab) + (size_t)row * (NT * entry_bytes) +
+                    (uint32_t)(wave * 64 * entry_bytes);
+    return *reinterpret_cast<const T*>(r + id * (uint32_t)entry_bytes);
   }
   // The thread's {LDS offset, logical index} bases of a layout, read from the
   // plan's per-thread table (a vector load through the caches).
-  __device__ __forceinline__ uint2 base2(int layout) const {
-    return thread_entry<uint2>(A.tbases, layout, sizeof(ThrBase));
+  __device__ __forceinline__ uint2 base2(int layout, uint32_t id) const {
+    return thread_entry<uint2>(A.tbases, layout, sizeof(ThrBase), id);
+  }
+  __device__ __forceinline__ uint2 base2(int layout) const { return base2(layout, lane_id()); }
+  // what the thread owes, from a row of the epoch table
+  __device__ __forceinline__ float2 owes(int row, uint32_t id) const {
+    return thread_entry<float2>(A.tab, row, sizeof(float2), id);
   }
   __device__ __forceinline__ uint32_t mem_base(int layout) const {
     return A.tbases[(size_t)layout * NT + t].mem;
@@ -442,95 +451,46 @@ struct PassCtx {
     return tlog | (layout == cur_idx ? cur.y : base2(layout).y);
   }
 
-  // op bodies, shared by the single ops and the fused epoch op.  bf, bt: the
-  // thread's LDS bases of the layouts before and after the exchange.
-  // rf, rt: the layouts' register contributions.
+  // op bodies, shared by the single ops and the fused epoch op.
+
+  // the pending phase into the amplitudes (an exact identity when none is pending)
+  __device__ __forceinline__ void flush(float2 (&a)[NA], float2 (&l)[NA], float2& ph) const {
+    scale_all<NA>(a, ph);
+    if constexpr (BWD) scale_all<NA>(l, ph);
+    ph = make_float2(1.f, 0.f);
+  }
+  // Flush, and the tile through LDS into another layout.  bf, bt: the thread's LDS bases
+  // before and after; rf, rt: the layouts' register contributions.
   __device__ __forceinline__ void perm(float2 (&a)[NA], float2 (&l)[NA], float2& ph, const RegBits<R>& rf,
                                        const RegBits<R>& rt, uint32_t bf, uint32_t bt) const {
-  // flush the pending phase (an exact identity when none is pending)
-  scale_all<NA>(a, ph);
-  if constexpr (BWD) scale_all<NA>(l, ph);
-  ph = make_float2(1.f, 0.f);
-  if (active) {
-#pragma unroll
-    for (int jj = 0; jj < NA; ++jj) lds_at(lds, bf ^ rf(jj)) = a[jj];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int jj = 0; jj < NA; ++jj) a[jj] = lds_at(lds, bt ^ rt(jj));
-  __syncthreads();
-  if constexpr (BWD) {
+    flush(a, l, ph);
     if (active) {
 #pragma unroll
-      for (int jj = 0; jj < NA; ++jj) lds_at(lds, bf ^ rf(jj)) = l[jj];
+      for (int jj = 0; jj < NA; ++jj) lds_at(lds, bf ^ rf(jj)) = a[jj];
     }
     __syncthreads();
 #pragma unroll
-    for (int jj = 0; jj < NA; ++jj) l[jj] = lds_at(lds, bt ^ rt(jj));
+    for (int jj = 0; jj < NA; ++jj) a[jj] = lds_at(lds, bt ^ rt(jj));
     __syncthreads();
-  }
+    if constexpr (BWD) {
+      if (active) {
+#pragma unroll
+        for (int jj = 0; jj < NA; ++jj) lds_at(lds, bf ^ rf(jj)) = l[jj];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int jj = 0; jj < NA; ++jj) l[jj] = lds_at(lds, bt ^ rt(jj));
+      __syncthreads();
+    }
   }
 
-  // A run group outside an epoch: bit j of mask has the run with coefficient ref refs[j]
-  // (the backward un-applies it: f -> -f).  Scaled rotations are scaled right away, so
-  // that functionals and expectations see the states themselves.
-  __device__ __forceinline__ void group(float2 (&a)[NA], float2 (&l)[NA], const int (&refs)[R], int mask) const {
-    float tt[R], sn[R];
-    double nrm = 1.0;   // the squared norm of the unscaled product, from the float tangents
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      tt[j] = 0.f;
-      sn[j] = 0.f;
-      if ((mask >> j) & 1) {
-        const float* cp = run_coef(A, refs[j], sample);
-        tt[j] = BWD ? -cld(cp + 6) : cld(cp + 6);
-        sn[j] = BWD ? -cld(cp + 1) : cld(cp + 1);
-        nrm *= fma((double)tt[j], (double)tt[j], 1.0);
-      }
-    }
-    apply_group<R>(a, tt, sn);
-    if constexpr (BWD) apply_group<R>(l, tt, sn);
-    if constexpr (kScaledRot<R>) {
-      const float sc = (float)rsqrt(nrm);
-#pragma unroll
-      for (int i = 0; i < NA; ++i) {
-        a[i].x *= sc;
-        a[i].y *= sc;
-        if constexpr (BWD) {
-          l[i].x *= sc;
-          l[i].y *= sc;
-        }
-      }
-    }
-  }
-  __device__ __forceinline__ void ry(float2 (&a)[NA], float2 (&l)[NA], int bit, int ref) const {
-    int refs[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) refs[j] = ref;
-    group(a, l, refs, 1 << bit);
-  }
-  __device__ __forceinline__ void ryg(float2 (&a)[NA], float2 (&l)[NA], int first, int mask) const {
-    const RygEntry* ge = A.rygs + first;
-    int refs[R], e = 0;
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      refs[j] = 0;
-      if ((mask >> j) & 1) refs[j] = cld(&ge[e++].ref);
-    }
-    group(a, l, refs, mask);
-  }
   // An epoch's run group: its coefficients stand in the epoch table, and the scale of
   // its shared runs in the table's pending factor; per-sample runs bring their own.
+  // tt, sn: the table row's coefficients.
   __device__ __forceinline__ void epoch_group(float2 (&a)[NA], float2 (&l)[NA], float2& ph, const EpochRec* E,
-                                              int tab, int ps_mask) const {
-    const float* row = A.tco + (size_t)tab * kTabCoefs;
-    float tt[R], sn[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      tt[j] = cld(row + j);
-      sn[j] = kScaledRot<R> ? 0.f : cld(row + 8 + j);
-    }
-    if (ps_mask) {
+                                              int flags, float (&tt)[R], float (&sn)[R]) const {
+    if (flags & kEpochPs) {
+      const int ps_mask = cld(&E->ps_mask);
       double nrm = 1.0;
 #pragma unroll
       for (int j = 0; j < R; ++j)
@@ -603,11 +563,10 @@ struct PassCtx {
   if constexpr (BWD) flip_signs<NA>(l, sign);
   }
 
-  __device__ __forceinline__ void phasea(float2 (&a)[NA], float2 (&l)[NA], float2& ph, int bit, int pev) const {
+  __device__ __forceinline__ void phasea(float2 (&a)[NA], float2 (&l)[NA], int bit, int ref) const {
     // diag(w, conj w) on register bit `bit`: the factor of slot jj is chosen
     // with a uniform select, so no code depends on the bit at compile time
-    const PhaseEv e = ld_pev(A.pev + pev);
-    float2 w = event_coef(A, e.ref, sample);
+    float2 w = event_coef(A, ref, sample);
     if (BWD) w.y = -w.y;
     const float2 wc = make_float2(w.x, -w.y);
 #pragma unroll
@@ -682,7 +641,7 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
   constexpr int WAVES = NT / 64;
   const int t = threadIdx.x;
   const int lane = t & 63;
-  const int wave = t >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int tb = A.tb;
   const bool active = t < (1 << tb);
   const int sl = item >> A.tiles_log2;
@@ -690,14 +649,20 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
   const int sample = A.sample0 + sl;
   const PassRec* P = A.prec;
 
+  // (the bit numbers are bytes, read as words through the scalar cache)
   uint32_t tlog = 0, tin = 0, tout = 0;
-  const int nnl = cld(&P->n_nonlocal);
-  for (int i = 0; i < nnl; ++i)
-    if ((tile >> i) & 1) {
-      tlog |= 1u << cld(&P->nl_log[i]);
-      tin |= 1u << cld(&P->nl_in[i]);
-      tout |= 1u << cld(&P->nl_out[i]);
+  for (int i = 0; i < A.tiles_log2; i += 4) {
+    const uint32_t wl = cld(reinterpret_cast<const uint32_t*>(P->nl_log + i));
+    const uint32_t wi = cld(reinterpret_cast<const uint32_t*>(P->nl_in + i));
+    const uint32_t wo = cld(reinterpret_cast<const uint32_t*>(P->nl_out + i));
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {   // (tile bits beyond tiles_log2 are zero)
+      const uint32_t bit = (uint32_t)(tile >> (i + b)) & 1u;
+      tlog |= bit << ((wl >> (8 * b)) & 31u);
+      tin |= bit << ((wi >> (8 * b)) & 31u);
+      tout |= bit << ((wo >> (8 * b)) & 31u);
     }
+  }
 
   float2 a[NA];
   float2 l[NA];
@@ -706,7 +671,7 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
     a[j] = make_float2(0.f, 0.f);
     l[j] = make_float2(0.f, 0.f);
   }
-  const int n_slots = cld(&P->n_slots);
+  const int n_slots = A.n_slots;
   // pending per-thread phase of the diagonal gates on thread-held qubits; it
   // multiplies psi (and, in the backward, lambda as well)
   float2 ph = make_float2(1.f, 0.f);
@@ -756,10 +721,7 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
         break;
       }
       case OP_STORE: {
-        // flush the pending phase (an exact identity when none is pending)
-        scale_all<NA>(a, ph);
-        if constexpr (BWD) scale_all<NA>(l, ph);
-        ph = make_float2(1.f, 0.f);
+        cx.flush(a, l, ph);
         const LayoutRec* L = A.layouts + op.a;
         const uint32_t base = (op.c ? tout : tin) | cx.mem_base(op.a);
         RegBits<R> rb;
@@ -802,12 +764,6 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
         cx.perm(a, l, ph, rf, rt, bf, cur.x);
         break;
       }
-      case OP_RY:
-        cx.ry(a, l, op.a, op.b);
-        break;
-      case OP_RYG:
-        cx.ryg(a, l, op.b, op.c);
-        break;
       case OP_DIAGT:
         cx.diagt(a, l, ph, cx.log_base(op.a, cur_idx, cur), op.b, op.c, op.d, op.e);
         break;
@@ -815,74 +771,95 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
         cx.cza(a, l, ph, op.a, cx.log_base(op.b, cur_idx, cur));
         break;
       case OP_PHASEA:
-        cx.phasea(a, l, ph, op.a, op.b);
+        cx.phasea(a, l, op.a, op.c);
         break;
       case OP_EPOCH: {
         // a run of consecutive register epochs, one iteration each, with the
-        // sub-steps of an epoch in program order; every epoch has its PERM and
-        // applies its run group (mask 0: identity), so the loop body has one path
-        for (int ei = op.a; ei < op.a + op.b; ++ei) {
-          const EpochRec* E = A.epochs + ei;
-          const int perm_from = cld(&E->perm_from), perm_to = cld(&E->perm_to);
-          const int tab = cld(&E->tab), ps_mask = cld(&E->ps_mask);
+        // sub-steps of an epoch in program order; every epoch applies its run group
+        // (absent bits: t = 0, the identity), so the loop body has one path.
+        // What an epoch reads has addresses that follow from its index: its thread
+        // entries are requested one epoch ahead, its record and coefficients are
+        // brought into the scalar cache one epoch ahead.  (One sample of 10 qubits is one
+        // wave on the device: each epoch waited for a chain of four reads.  Forward passes
+        // 57 -> 46 us per launch; 12 qubits x 100 layers x 1,024 samples 2.95 -> 2.83 ms;
+        // no change at 20 qubits, where other waves hide the reads.)
+        constexpr int kStep = BWD ? -1 : 1;
+        if (op.e != cur_idx) cur = cx.base2(op.e);
+        uint2 nb_next = cx.base2(op.d);
+        float2 owed_next = cx.owes(op.c, cx.lane_id());
+        if constexpr (BWD) cmul_in(ph, make_float2(owed_next.x, -owed_next.y));
+        for (int i = 0; i < op.b; ++i) {
+          const EpochRec* E = A.epochs + op.a + i;
           RegBits<R> rf, rt;
           rf.load(E->lds_from);
           rt.load(E->lds_to);
-          const int czg_loop = cld(&E->czg_loop), pev_loop = cld(&E->pev_loop);
-          const int n_pha = cld(&E->pha_count), pha0 = cld(&E->pha_first);
-          const int cza = cld(&E->cza), cza_layout = cld(&E->cza_layout);
-          // what the thread owes when this epoch's exchange sends its amplitudes: one
-          // table entry in place of the epoch's diagonal items and scale factors
-          const float2 owed = cx.template thread_entry<float2>(A.tab, tab, sizeof(float2));
-          if constexpr (!BWD) {
-            // bases before the PERM: carried from the previous epoch (the planner chains
-            // the layouts; the load is a fallback), requested before those after it so
-            // that the LDS writes wait for the first load only
-            uint32_t bf = cur.x;
-            if (perm_from != cur_idx) bf = cx.base2(perm_from).x;
-            const uint2 nb = cx.base2(perm_to);
-            cx.perm(a, l, ph, rf, rt, bf, nb.x);
-            cur = nb;
-            cur_idx = perm_to;
-            ph = owed;
-            if (czg_loop | pev_loop)
-              cx.diagt(a, l, ph, cx.log_base(cld(&E->diag_layout), cur_idx, cur), cld(&E->czg_first), czg_loop,
-                       cld(&E->pev_first), pev_loop);
-            for (int p = pha0; p < pha0 + n_pha; ++p) cx.phasea(a, l, ph, cld(&A.phas[p].regbit), cld(&A.phas[p].pev));
-            if (cza >= 0) cx.cza(a, l, ph, cza, cx.log_base(cza_layout, cur_idx, cur));
-            cx.epoch_group(a, l, ph, E, tab, ps_mask);
-          } else {
-            // the tile is in layout perm_from until the PERM that ends the epoch
-            if (perm_from != cur_idx) {
-              cur = cx.base2(perm_from);
-              cur_idx = perm_from;
-            }
-            // bases after the PERM, requested now: the epoch's work hides the load
-            const uint2 nb = cx.base2(perm_to);
-            int sl[R];
+          int sl[R];
 #pragma unroll
-            for (int j = 0; j < R; ++j) sl[j] = cld(&E->slot[j]);
+          for (int j = 0; j < R; ++j) sl[j] = BWD ? cld(&E->slot[j]) : 0;
+          const int flags = cld(&E->flags);
+          const float* row = A.tco + (size_t)(op.c + kStep * i) * kTabCoefs;
+          float tt[R], sn[R];
+#pragma unroll
+          for (int j = 0; j < R; ++j) {
+            tt[j] = cld(row + j);
+            sn[j] = kScaledRot<R> ? 0.f : cld(row + 8 + j);
+          }
+          // nb: the thread's bases after the exchange; owed: what it owes when this epoch's
+          // exchange sends its amplitudes, one table entry in place of the epoch's
+          // diagonal items and scale factors
+          const uint2 nb = nb_next;
+          [[maybe_unused]] const float2 owed = owed_next;
+          const int in = min(i + 1, op.b - 1);   // (the last epoch reads its own again)
+          const uint32_t id = cx.lane_id();
+          nb_next = cx.base2(op.d + kStep * in, id);
+          owed_next = cx.owes(op.c + kStep * in, id);
+          const int warm = cld(&(A.epochs + op.a + in)->flags) ^
+                           __float_as_int(cld(A.tco + (size_t)(op.c + kStep * in) * kTabCoefs));
+          asm volatile("" ::"s"(warm));
+          if constexpr (!BWD) {
+            if (flags & kEpochStay) cx.flush(a, l, ph);
+            else cx.perm(a, l, ph, rf, rt, cur.x, nb.x);
+            cur = nb;
+            ph = owed;
+            if (flags) {
+              if (flags & kEpochLoop)
+                cx.diagt(a, l, ph, cx.tlog | cur.y, cld(&E->czg_first), cld(&E->czg_loop), cld(&E->pev_first),
+                         cld(&E->pev_loop));
+              if (flags & kEpochPhaseA)
+                for (int p = cld(&E->pha_first), pe = p + cld(&E->pha_count); p < pe; ++p)
+                  cx.phasea(a, l, cld(&A.phas[p].regbit), cld(&A.phas[p].ref));
+              if (flags & kEpochCza) cx.cza(a, l, ph, cld(&E->cza), cx.tlog | cur.y);
+            }
+            cx.epoch_group(a, l, ph, E, flags, tt, sn);
+          } else {
+            // the tile is in the layout before the PERM that ends the epoch
             cx.func(a, l, sl);
-            cx.epoch_group(a, l, ph, E, tab, ps_mask);
-            if (cza >= 0) cx.cza(a, l, ph, cza, cx.log_base(cza_layout, cur_idx, cur));
-            for (int p = pha0; p < pha0 + n_pha; ++p) cx.phasea(a, l, ph, cld(&A.phas[p].regbit), cld(&A.phas[p].pev));
-            if (czg_loop | pev_loop)
-              cx.diagt(a, l, ph, cx.log_base(cld(&E->diag_layout), cur_idx, cur), cld(&E->czg_first), czg_loop,
-                       cld(&E->pev_first), pev_loop);
-            cmul_in(ph, make_float2(owed.x, -owed.y));
+            cx.epoch_group(a, l, ph, E, flags, tt, sn);
+            if (flags) {
+              if (flags & kEpochCza) cx.cza(a, l, ph, cld(&E->cza), cx.tlog | cur.y);
+              if (flags & kEpochPhaseA)
+                for (int p = cld(&E->pha_first), pe = p + cld(&E->pha_count); p < pe; ++p)
+                  cx.phasea(a, l, cld(&A.phas[p].regbit), cld(&A.phas[p].ref));
+              if (flags & kEpochLoop)
+                cx.diagt(a, l, ph, cx.tlog | cur.y, cld(&E->czg_first), cld(&E->czg_loop), cld(&E->pev_first),
+                         cld(&E->pev_loop));
+            }
+            // (kEpochStay: an exchange with itself, once per pass; a branch around it
+            // made the compiler spill, 8% at 20 qubits)
             cx.perm(a, l, ph, rf, rt, cur.x, nb.x);
             cur = nb;
-            cur_idx = perm_to;
+            ph = make_float2(owed_next.x, -owed_next.y);
           }
         }
+        if constexpr (BWD) ph = make_float2(1.f, 0.f);   // (the last epoch's owed factor once more)
+        cur_idx = op.d + kStep * (op.b - 1);
         break;
       }
       case OP_EXPECT: {
         if constexpr (!BWD) {
           if (!A.do_expect) break;
           // the pending factor may hold scale factors
-          scale_all<NA>(a, ph);
-          ph = make_float2(1.f, 0.f);
+          cx.flush(a, l, ph);
           const LayoutRec* L = A.layouts + op.a;
           const uint32_t base = cx.log_base(op.a, cur_idx, cur);
           RegBits<R> rb;
@@ -931,14 +908,6 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
         }
         break;
       }
-      case OP_FUNC:
-        {
-          int sl[R];
-#pragma unroll
-          for (int j = 0; j < R; ++j) sl[j] = cld(&(A.funcs + op.b)[j].slot);
-          cx.func(a, l, sl);
-        }
-        break;
       default:
         break;
     }

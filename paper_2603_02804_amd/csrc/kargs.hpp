@@ -58,8 +58,6 @@ struct KArgs {
   const LayoutRec* layouts;
   const ThrBase* tbases;      // [layout][NT] thread bases of every layout
   const CzGroup* czg;
-  const FuncEntry* funcs;
-  const RygEntry* rygs;
   const EpochRec* epochs;
   const PhaEntry* phas;
   const PassRec* prec;
@@ -87,7 +85,7 @@ struct KArgs {
   int tiles_log2;
   int tb;                     // thread bits of the tile
   int do_expect;
-  int tile_elems;             // 2^k: LDS elements of the tile; wave partial sums follow
+  int n_slots;                // functional slots of the pass
   uint32_t* dst2;             // forward: bfloat16-pair copy of the output (memory-saving mode)
   long long sd2;              // its per-sample stride (words)
   int src0_bf16;              // psi input as bfloat16 pairs (4 bytes per amplitude)
@@ -131,8 +129,6 @@ inline KArgs make_pass_args(const PlanCore& c, const PlanPtrs& d, const CoefPtrs
   A.layouts = d.layouts;
   A.tbases = d.tbases;
   A.czg = d.czg;
-  A.funcs = d.funcs;
-  A.rygs = d.rygs;
   A.epochs = d.epochs;
   A.phas = d.phas;
   A.prec = d.passes + L.pass;
@@ -166,7 +162,7 @@ inline KArgs make_pass_args(const PlanCore& c, const PlanPtrs& d, const CoefPtrs
   A.tiles_log2 = S.tiles_log2;
   A.tb = S.thread_bits;
   A.do_expect = L.do_expect;
-  A.tile_elems = 1 << S.k;
+  A.n_slots = pr.n_slots;
   return A;
 }
 

@@ -279,11 +279,10 @@ static void group_register_runs(Schedule* Sp) {
   S.ops.swap(out);
 }
 
-// Folds each register epoch into one OP_EPOCH op.  Forward: a PERM, then
-// optionally a DIAGT, PHASEA ops, a CZA and one RY / RYG, in that order.
-// Backward: optionally a FUNC, one RY / RYG, a CZA, PHASEA ops and a DIAGT,
-// ending with a PERM.  The sub-ops keep their order, so execution is unchanged;
-// ops outside these patterns stay as they are.
+// Folds each register epoch into one OP_EPOCH op.  Forward: optionally a PERM, a DIAGT,
+// PHASEA ops and a CZA, then one RY / RYG, in that order.  Backward: optionally a FUNC,
+// one RY / RYG, then optionally a CZA, PHASEA ops, a DIAGT and a PERM.  The sub-ops keep
+// their order, so execution is unchanged; ops without a run group stay as they are.
 static void fuse_epochs(Schedule* Sp) {
   Schedule& S = *Sp;
   std::vector<Op> out;
@@ -309,7 +308,7 @@ static void fuse_epochs(Schedule* Sp) {
   auto take_phas = [&](int* j, int end, EpochRec* e) {
     e->pha_first = (int)S.phas.size();
     while (*j < end && S.ops[*j].kind == OP_PHASEA) {
-      S.phas.push_back({S.ops[*j].a, S.ops[*j].b});
+      S.phas.push_back({S.ops[*j].a, S.ops[*j].b, S.ops[*j].c, 0});
       ++*j;
     }
     e->pha_count = (int)S.phas.size() - e->pha_first;
@@ -318,13 +317,14 @@ static void fuse_epochs(Schedule* Sp) {
     e->diag_layout = o.a; e->czg_first = o.b; e->czg_count = o.c; e->pev_first = o.d; e->pev_count = o.e;
     e->czg_loop = o.f; e->pev_loop = o.g;
   };
-  // consecutive epochs share one OP_EPOCH op (records are contiguous)
-  // Every exchange makes a layout of its own, so a forward epoch and its mirror share
-  // the layout of their run group, and with it the table row.
+  // consecutive epochs share one OP_EPOCH op (records are contiguous, and table rows
+  // and layouts count up or down by one)
+  // A forward epoch and its mirror share their run group, and with it the table row: a
+  // run has a coefficient ref of its own.
   std::map<int, int> tab_of;
   auto complete = [&](EpochRec* e, int layout) {
     for (int j = 0; j < S.R; ++j) {
-      e->lds_from[j] = S.layouts[e->perm_from].lds_reg[j];
+      e->lds_from[j] = S.layouts[e->perm_from >= 0 ? e->perm_from : e->perm_to].lds_reg[j];
       e->lds_to[j] = S.layouts[e->perm_to].lds_reg[j];
     }
     for (int j = 0; j < kMaxR; ++j)
@@ -340,7 +340,10 @@ static void fuse_epochs(Schedule* Sp) {
         if (ref >= 0) t.ref[j] = ref;
         else e->ps_mask |= 1 << j;
       }
-    auto f = tab_of.find(layout);
+    e->flags = (e->perm_from < 0 ? kEpochStay : 0) | (e->ps_mask ? kEpochPs : 0) | (e->czg_loop | e->pev_loop ? kEpochLoop : 0) |
+               (e->pha_count > 0 ? kEpochPhaseA : 0) | (e->cza >= 0 ? kEpochCza : 0);
+    const int key = S.rygs[e->ry_a].ref;
+    auto f = tab_of.find(key);
     if (f != tab_of.end()) {
       e->tab = f->second;
       return;
@@ -352,50 +355,49 @@ static void fuse_epochs(Schedule* Sp) {
     t.czg_count = e->czg_count - e->czg_loop;
     t.pha_first = e->pha_first;
     t.pha_count = e->pha_count;
-    e->tab = tab_of[layout] = (int)S.tabs.size();
+    e->tab = tab_of[key] = (int)S.tabs.size();
     S.tabs.push_back(t);
   };
-  auto emit = [&](const EpochRec& e) {
-    if (!out.empty() && out.back().kind == OP_EPOCH && out.back().a + out.back().b == (int)S.epochs.size() &&
-        (int)out.size() > cur_begin)
+  auto emit = [&](EpochRec* e, int step) {
+    complete(e, step > 0 || e->perm_from < 0 ? e->perm_to : e->perm_from);
+    const EpochRec* p = S.epochs.empty() ? nullptr : &S.epochs.back();
+    if ((int)out.size() > cur_begin && out.back().kind == OP_EPOCH &&
+        out.back().a + out.back().b == (int)S.epochs.size() && e->tab == p->tab + step &&
+        e->perm_to == p->perm_to + step && e->perm_from == p->perm_to)
       out.back().b++;
     else
-      out.push_back({OP_EPOCH, (int)S.epochs.size(), 1, 0, 0, 0, 0, 0});
-    S.epochs.push_back(e);
+      out.push_back({OP_EPOCH, (int)S.epochs.size(), 1, e->tab, e->perm_to,
+                     e->perm_from >= 0 ? e->perm_from : e->perm_to, 0, 0});
+    S.epochs.push_back(*e);
   };
+  // layout: the one the tile is in
+  auto is_run = [&](int i, int end) { return i < end && (S.ops[i].kind == OP_RY || S.ops[i].kind == OP_RYG); };
   auto fwd = [&](int begin, int count, int* nb, int* nc) {
     *nb = (int)out.size();
     cur_begin = *nb;
     const int end = begin + count;
-    int i = begin;
+    int i = begin, layout = -1;
     while (i < end) {
-      if (S.ops[i].kind != OP_PERM) { out.push_back(S.ops[i++]); continue; }
+      const int k = S.ops[i].kind;
+      if (k == OP_LOAD || k == OP_INIT0) layout = S.ops[i].a;
       EpochRec e = blank();
-      e.perm_from = S.ops[i].a;
-      e.perm_to = S.ops[i].b;
-      int j = i + 1;
+      int j = i;
+      if (k == OP_PERM) {
+        e.perm_from = S.ops[j].a;
+        layout = S.ops[j++].b;
+      }
+      e.perm_to = layout;
       if (j < end && S.ops[j].kind == OP_DIAGT) take_diag(S.ops[j++], &e);
       take_phas(&j, end, &e);
-      if (e.pha_count > kEpochMaxPhaseA) {   // rare: leave this epoch's ops as they are
-        S.phas.resize(e.pha_first);
-        for (int q = i; q < j; ++q) out.push_back(S.ops[q]);
-        i = j;
-        continue;
-      }
       if (j < end && S.ops[j].kind == OP_CZA) { e.cza = S.ops[j].a; e.cza_layout = S.ops[j].b; ++j; }
-      if (j < end && (S.ops[j].kind == OP_RY || S.ops[j].kind == OP_RYG)) {
+      if (is_run(j, end)) {
         take_ry(S.ops[j++], &e);
-      } else {
-        // no runs (the exchange into the store layout at the end of a pass): its ops
-        // stay single, so the epoch loop never applies an empty run group (as the
-        // adjoint program, which fuses from its runs, leaves them too)
+        emit(&e, 1);
+      } else {   // no runs: the ops stay single
         S.phas.resize(e.pha_first);
+        if (j == i) ++j;
         for (int q = i; q < j; ++q) out.push_back(S.ops[q]);
-        i = j;
-        continue;
       }
-      complete(&e, e.perm_to);
-      emit(e);
       i = j;
     }
     *nc = (int)out.size() - *nb;
@@ -404,33 +406,28 @@ static void fuse_epochs(Schedule* Sp) {
     *nb = (int)out.size();
     cur_begin = *nb;
     const int end = begin + count;
-    int i = begin;
+    int i = begin, layout = -1;
     while (i < end) {
       const int k = S.ops[i].kind;
-      if (k != OP_FUNC && k != OP_RY && k != OP_RYG) { out.push_back(S.ops[i++]); continue; }
+      if (k == OP_LOAD) layout = S.ops[i].a;
+      if (k == OP_PERM) layout = S.ops[i].b;
+      if (k != OP_FUNC && !is_run(i, end)) { out.push_back(S.ops[i++]); continue; }
       EpochRec e = blank();
       int j = i;
-      if (S.ops[j].kind == OP_FUNC) {
+      if (k == OP_FUNC) {
         e.func_count = S.ops[j].a; e.func_first = S.ops[j].b; e.func_full = S.ops[j].c;
         ++j;
       }
-      if (j < end && (S.ops[j].kind == OP_RY || S.ops[j].kind == OP_RYG)) take_ry(S.ops[j++], &e);
+      take_ry(S.ops[j++], &e);
       if (j < end && S.ops[j].kind == OP_CZA) { e.cza = S.ops[j].a; e.cza_layout = S.ops[j].b; ++j; }
       take_phas(&j, end, &e);
       if (j < end && S.ops[j].kind == OP_DIAGT) take_diag(S.ops[j++], &e);
-      if (!(j < end && S.ops[j].kind == OP_PERM) || e.pha_count > kEpochMaxPhaseA) {
-        // epochs are fused only with their PERM; otherwise the ops stay as they are
-        S.phas.resize(e.pha_first);
-        if (e.ry_kind == 2 && S.ops[i + (S.ops[i].kind == OP_FUNC ? 1 : 0)].kind == OP_RY) S.rygs.pop_back();
-        for (int q = i; q < j; ++q) out.push_back(S.ops[q]);
-        i = j;
-        continue;
+      if (j < end && S.ops[j].kind == OP_PERM) {
+        e.perm_from = S.ops[j].a;
+        layout = S.ops[j++].b;
       }
-      e.perm_from = S.ops[j].a;
-      e.perm_to = S.ops[j].b;
-      ++j;
-      complete(&e, e.perm_from);
-      emit(e);
+      e.perm_to = layout;
+      emit(&e, -1);
       i = j;
     }
     *nc = (int)out.size() - *nb;
@@ -720,7 +717,7 @@ static bool build_with_fill(const Circuit& C, const Tuning& T, Schedule* Sp, std
           int j = (int)(std::find(regq.begin(), regq.end(), it.q0) - regq.begin());
           const int eb = (int)S.pev.size();
           S.pev.push_back(S.pev[it.ev]);
-          S.ops.push_back({OP_PHASEA, j, eb, 0, 0, 0, 0, 0});
+          S.ops.push_back({OP_PHASEA, j, eb, S.pev[eb].ref, 0, 0, 0, 0});
         }
       }
       if (edges.empty()) return;

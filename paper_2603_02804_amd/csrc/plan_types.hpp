@@ -39,7 +39,8 @@ enum OpKind : int32_t {
                   // diagonal gates on thread-held qubits, folded into the pending phase; the
                   // first f groups and g events involve other tiles or per-sample angles
   OP_CZA = 7,     // a=CzaRec, b=layout: CZ signs for edges touching register bits
-  OP_PHASEA = 8,  // a=register bit, b=phase event: RZ phase on a register-held qubit
+  OP_PHASEA = 8,  // a=register bit, b=phase event, c=its coefficient ref: RZ phase on a
+                  // register-held qubit
   OP_EXPECT = 9,  // a=layout: Z-string expectations of psi -> partial sums
   OP_SEED = 10,   // a=layout: lambda = 2 sum_k g_k O_k psi
   OP_FUNC = 11,   // a=R entries, b=first FuncEntry (entry j: register bit j, slot or -1):
@@ -48,7 +49,9 @@ enum OpKind : int32_t {
                   // several runs on distinct register bits (they commute), bits ascending
   OP_EPOCH = 13,  // a=first EpochRec, b=count: consecutive register epochs (PERM, DIAGT,
                   // PHASEA*, CZA, RY group forward; FUNC, RY group, CZA, PHASEA*, DIAGT,
-                  // PERM backward), one loop iteration each
+                  // PERM backward), one loop iteration each.  c, d, e: table row, layout
+                  // after and before the exchange of the first epoch; row and layout go up
+                  // by one per epoch forward and down by one backward
 };
 
 struct Op {
@@ -135,33 +138,37 @@ struct RygEntry {
   int32_t regbit, ref;
 };
 
-// PHASEA inside an epoch: register bit and phase event.
+// PHASEA inside an epoch: register bit, phase event and its coefficient ref.
 struct PhaEntry {
-  int32_t regbit, pev;
+  int32_t regbit, pev, ref, pad;
 };
 
-// The sub-ops of one epoch; -1 / 0 fields mark sub-ops that are absent.  At
-// most kEpochMaxPhaseA PHASEA sub-ops (epochs with more stay unfused; they are
-// diagonal, so their order within the epoch does not matter).  What the kernels
+// The sub-ops of one epoch; -1 / 0 fields mark sub-ops that are absent.  Every run
+// group belongs to one; without a PERM (kEpochStay: the group that a pass starts with, or
+// one in the layout of the group before) the pending phase is flushed where the tile
+// stands.  What the kernels
 // need of other tables is repeated here, so that an epoch's scalar reads depend on
 // its index alone and not on one another.
-constexpr int kEpochMaxPhaseA = 8;
+enum EpochFlags : int32_t { kEpochPs = 1, kEpochLoop = 2, kEpochPhaseA = 4, kEpochCza = 8, kEpochStay = 16 };
 struct EpochRec {
-  int32_t perm_from, perm_to;                          // PERM (from -1: none)
-  int32_t tab;                                         // row of the epoch tables (TabRec)
-  int32_t ps_mask;                                     // register bits whose run is per-sample
+  // one cache line: all that an epoch without any of the flagged sub-ops reads
   uint32_t lds_from[kMaxR], lds_to[kMaxR];             // lds_reg of the two layouts
   int32_t slot[kMaxR];                                 // FUNC: functional slot per register bit, or -1
+  int32_t flags;                                       // EpochFlags: the sub-ops below that are present
+  int32_t ps_mask;                                     // register bits whose run is per-sample
   int32_t ref[kMaxR];                                  // run group: coefficient ref per register bit (absent: 0)
   int32_t diag_layout, czg_first, czg_count, pev_first, pev_count;   // DIAGT (layout -1: none)
   int32_t czg_loop, pev_loop;                          // the first of them that the pass kernel forms;
                                                        // the epoch table holds the others
   int32_t pha_first, pha_count;                        // PhaEntry range
   int32_t cza, cza_layout;                             // CZA (-1: none)
+  int32_t perm_from, perm_to;                          // PERM (from -1: none, to: the layout)
+  int32_t tab;                                         // row of the epoch tables (TabRec)
   int32_t ry_kind, ry_a, ry_b;                         // run group: first RygEntry a, bit mask b (0: none)
   int32_t func_count, func_first, func_full;           // FUNC (backward; func_full unused)
-  int32_t pad[7];
+  int32_t pad[6];
 };
+static_assert(sizeof(EpochRec) % 64 == 0, "epoch records are whole cache lines");
 
 // One row of the epoch tables, formed once per call by the coefficient kernels and
 // shared by all samples and tiles.  For every thread of the layout: the product of the

@@ -798,7 +798,8 @@ static int64_t lds_bank_degree(const Schedule& S) {
   for (const Op& o : S.ops) {
     if (o.kind == OP_PERM) perm(o.a, o.b);
     if (o.kind == OP_EPOCH)
-      for (int e = o.a; e < o.a + o.b; ++e) perm(S.epochs[e].perm_from, S.epochs[e].perm_to);
+      for (int e = o.a; e < o.a + o.b; ++e)
+        if (S.epochs[e].perm_from >= 0) perm(S.epochs[e].perm_from, S.epochs[e].perm_to);
   }
   return worst;
 }

@@ -52,7 +52,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_coef(const CoefArgsT<Real> a)
 }
 
 __global__ __launch_bounds__(kSmallThreads) void k_event_coef(const EventArgs a) {
-  event_body(a, blockIdx.x, threadIdx.x);
+  __shared__ double red[kCarryRows];
+  event_body(a, blockIdx.x, threadIdx.x, red);
 }
 
 __global__ __launch_bounds__(kSmallThreads) void k_fsum(const FsumArgs a) {

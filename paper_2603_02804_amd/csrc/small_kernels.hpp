@@ -188,12 +188,37 @@ __device__ inline float2 shared_event(const double* dsh, const EventRec& e) {
   return make_float2((float)wr, (float)wi);
 }
 
+// The scale that a row of the epoch tables owes: of its shared runs' rotations, and of
+// the rounded norms of the phases that it applies to register-held qubits.
+__device__ inline double row_scale(const EventArgs& a, const TabRec* r) {
+  double scale = 1.0;
+#pragma unroll
+  for (int j = 0; j < kMaxR; ++j)
+    if (r->ref[j] != INT32_MIN) scale *= a.dsh[kDshRow * (long long)r->ref[j] + 4];
+  for (int i = 0; i < r->pha_count; ++i) {
+    const int ref = a.phas[r->pha_first + i].ref;
+    if (ref < 0) continue;
+    const float2 w = shared_event(a.dsh, a.T.events[ref]);
+    scale /= sqrt((double)w.x * w.x + (double)w.y * w.y);
+  }
+  return scale;
+}
+
 // One entry of the epoch tables (TabRec): the factor that thread t of the row's layout
 // owes when the epoch's exchange sends its amplitudes, formed in double precision and
-// rounded once; and, by the first threads, the row's run coefficients.
-__device__ inline void table_body(const EventArgs& a, long long idx) {
-  if (idx >= (long long)a.n_tab * a.NT) return;
+// rounded once; and, by the first threads, the row's run coefficients.  The
+// scale's own rounding would change all amplitudes alike, with the same sign in many rows
+// (1/sqrt(2) of a CNOT's quarter turn: -1.7e-8): every row also owes what that of the rows
+// before it left, from the last multiple of kCarryRows on.  A workgroup's rows lie in one
+// such window; its first threads form the window's scales.
+constexpr int kCarryRows = 8;
+__device__ inline void table_body(const EventArgs& a, int blk, int thread, double* scales) {
+  const long long idx = (long long)blk * kSmallThreads + thread;
   const int row = (int)(idx / a.NT), t = (int)(idx - (long long)row * a.NT);
+  const int window = (int)((long long)blk * kSmallThreads / a.NT) / kCarryRows * kCarryRows;
+  if (thread < kCarryRows && window + thread < a.n_tab) scales[thread] = row_scale(a, a.trecs + window + thread);
+  __syncthreads();
+  if (row >= a.n_tab) return;
   const TabRec* r = a.trecs + row;
   const uint32_t x = a.tbases[(size_t)r->layout * a.NT + t].log;
   uint32_t par = 0;
@@ -218,16 +243,12 @@ __device__ inline void table_body(const EventArgs& a, long long idx) {
       wr = tr;
     }
   }
-  double scale = 1.0;
-#pragma unroll
-  for (int j = 0; j < kMaxR; ++j)
-    if (r->ref[j] != INT32_MIN) scale *= a.dsh[kDshRow * (long long)r->ref[j] + 4];
-  // phases that the epoch applies to register-held qubits: their rounded factors' norms
-  for (int i = 0; i < r->pha_count; ++i) {
-    const PhaseEv p = a.pev[a.phas[r->pha_first + i].pev];
-    if (p.ref < 0) continue;
-    const float2 w = shared_event(a.dsh, a.T.events[p.ref]);
-    scale /= sqrt((double)w.x * w.x + (double)w.y * w.y);
+  // (the scale itself is rounded before it turns, so that its remainder is known)
+  double carry = 1.0, scale = 1.0;
+  for (int q = window; q <= row; ++q) {
+    const double owed = carry * scales[q - window];
+    scale = (double)(float)owed;
+    carry = owed / scale;
   }
   a.tab[2 * idx] = (float)(scale * wr);
   a.tab[2 * idx + 1] = (float)(scale * wi);
@@ -288,13 +309,13 @@ __device__ inline void gvec_body(const EventArgs& a, int idx) {
 
 // Phase event coefficients w = u(prev run) * v(next run); the blocks after the events'
 // form the epoch tables.
-__device__ inline void event_body(const EventArgs& a, int blk, int thread) {
+__device__ inline void event_body(const EventArgs& a, int blk, int thread, double* red) {
   const long long rows = a.n_ev_sh + (long long)a.n_ev_ps * a.B;
   const int ev_blocks = (int)((rows + kSmallThreads - 1) / kSmallThreads);
   if (blk >= ev_blocks) {
     const int tab_blocks = (int)(((long long)a.n_tab * a.NT + kSmallThreads - 1) / kSmallThreads);
     blk -= ev_blocks;
-    if (blk < tab_blocks) table_body(a, (long long)blk * kSmallThreads + thread);
+    if (blk < tab_blocks) table_body(a, blk, thread, red);
     else gvec_body(a, (blk - tab_blocks) * kSmallThreads + thread);
     return;
   }
