@@ -242,6 +242,23 @@ __device__ __forceinline__ void func_xy_all(const float2 (&a)[1 << R], const flo
   }
 }
 
+// Im<l|Y_q|a> alone: four fused multiply-adds per pair.
+template <int R, int J = 0>
+__device__ __forceinline__ void func_y_all(const float2 (&a)[1 << R], const float2 (&l)[1 << R], float (&v)[2 * R]) {
+  if constexpr (J < R) {
+    float fy = v[2 * J];
+#pragma unroll
+    for (int i = 0; i < (1 << R); ++i) {
+      if (i & (1 << J)) continue;
+      constexpr int m = 1 << J;
+      const float2 p0 = a[i], p1 = a[i | m], l0 = l[i], l1 = l[i | m];
+      fy = fmaf(l1.x, p0.x, fy); fy = fmaf(l1.y, p0.y, fy); fy = fmaf(-l0.x, p1.x, fy); fy = fmaf(-l0.y, p1.y, fy);
+    }
+    v[2 * J] = fy;
+    func_y_all<R, J + 1>(a, l, v);
+  }
+}
+
 template <int NA>
 __device__ __forceinline__ void scale_all(float2 (&a)[NA], float2 p) {
 #pragma unroll
@@ -346,6 +363,26 @@ __device__ __forceinline__ float wave_reduce12(float (&v)[12], int lane) {
     const bool hi = (lane & 2) != 0;
     v[0] = sum_split(v[0], v[1], dpp_mov<kDppQuadXor2>(v[0]), dpp_mov<kDppQuadXor2>(v[1]), hi);
   }
+  v[0] += dpp_mov<kDppRowRor8>(v[0]);
+  v[0] += dpp_mov<kDppRowRor4>(v[0]);
+  return v[0];
+}
+
+// Reduce-scatter of 8 per-lane values (the Y and Z functionals of four register bits,
+// v[2 e + p]) over a wave of 64 lanes: lane bits 5 and 4 give e, lane bit 0 gives p.
+__device__ __forceinline__ float wave_reduce8(float (&v)[8], int lane) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 4]), false, false);
+    v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 2]), false, false);
+    v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  v[0] = sum_split(v[0], v[1], dpp_mov<kDppQuadXor1>(v[0]), dpp_mov<kDppQuadXor1>(v[1]), (lane & 1) != 0);
+  v[0] += dpp_mov<kDppQuadXor2>(v[0]);
   v[0] += dpp_mov<kDppRowRor8>(v[0]);
   v[0] += dpp_mov<kDppRowRor4>(v[0]);
   return v[0];
@@ -578,36 +615,60 @@ struct PassCtx {
   }
   // Im<lambda|P_q|psi> (P = X, Y, Z) of m register bits: wave sums into LDS
   // sl[j]: the slot of register bit j's run, or -1 when the bit holds no run of the group.
-  __device__ __forceinline__ void func(const float2 (&a)[NA], const float2 (&l)[NA], const int (&sl)[R]) const {
+  // no_x: the X functionals are zero by structure (kEpochNoX): 137 of about 815
+  // instructions of the adjoint epoch less (12 qubits x 100 layers of RY, RZ: 2.84 -> 2.68
+  // ms per step).
+  __device__ __forceinline__ void func(const float2 (&a)[NA], const float2 (&l)[NA], const int (&sl)[R],
+                                       bool no_x) const {
     if constexpr (BWD) {
       // part[wave][slot][Pauli], through an LDS-typed pointer
       __attribute__((address_space(3))) float* part = (__attribute__((address_space(3))) float*)qf_pass_part;
       if constexpr (R == 4) {
-        float v[12];
         float z[R];
         func_z_all<R>(a, l, z);
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-          v[3 * j] = v[3 * j + 1] = 0.f;
-          v[3 * j + 2] = z[j];
-        }
-        func_xy_all<R>(a, l, v);
         // lanes beyond a small tile hold copies of in-tile elements: no share
         // (workgroups of more than 64 threads always cover whole tiles)
-        if constexpr (NT == 64) {
-          if (A.tb < 6 && !active) {
+        const bool idle = NT == 64 && A.tb < 6 && !active;
+        float sum;
+        int pauli;
+        if (no_x) {
+          float v[8];
 #pragma unroll
-            for (int i = 0; i < 12; ++i) v[i] = 0.f;
+          for (int j = 0; j < R; ++j) {
+            v[2 * j] = 0.f;
+            v[2 * j + 1] = z[j];
           }
+          func_y_all<R>(a, l, v);
+          if constexpr (NT == 64) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = idle ? 0.f : v[i];
+          }
+          sum = wave_reduce8(v, lane);
+          // (the writer lanes of wave_reduce12: those of X write zero)
+          if (lane & 2) sum = 0.f;
+          pauli = (lane & 2) ? 0 : 1 + (lane & 1);
+        } else {
+          float v[12];
+#pragma unroll
+          for (int j = 0; j < R; ++j) {
+            v[3 * j] = v[3 * j + 1] = 0.f;
+            v[3 * j + 2] = z[j];
+          }
+          func_xy_all<R>(a, l, v);
+          if constexpr (NT == 64) {
+#pragma unroll
+            for (int i = 0; i < 12; ++i) v[i] = idle ? 0.f : v[i];
+          }
+          sum = wave_reduce12(v, lane);
+          pauli = wave_sum_pauli12(lane);
         }
-        const float sum = wave_reduce12(v, lane);
         // the slots of bits 0,1 and 2,3 as 16-bit halves (no run: 0xffff); a
         // lane picks its half with lane bits 5 and 4, which give its register bit
         const uint32_t slots01 = ((uint32_t)sl[0] & 0xffffu) | ((uint32_t)sl[1] << 16);
         const uint32_t slots23 = ((uint32_t)sl[2] & 0xffffu) | ((uint32_t)sl[3] << 16);
         const uint32_t slot = (((lane & 32) ? slots23 : slots01) >> (lane & 16)) & 0xffffu;
         if (wave_sum_writer12(lane) && slot != 0xffffu)
-          part[wave * 3 * n_slots + 3 * (int)slot + wave_sum_pauli12(lane)] = sum;
+          part[wave * 3 * n_slots + 3 * (int)slot + pauli] = sum;
       } else {
         float v[16];
 #pragma unroll
@@ -821,7 +882,7 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
             else cx.perm(a, l, ph, rf, rt, cur.x, nb.x);
             cur = nb;
             ph = owed;
-            if (flags) {
+            if (flags & (kEpochLoop | kEpochPhaseA | kEpochCza)) {
               if (flags & kEpochLoop)
                 cx.diagt(a, l, ph, cx.tlog | cur.y, cld(&E->czg_first), cld(&E->czg_loop), cld(&E->pev_first),
                          cld(&E->pev_loop));
@@ -833,9 +894,9 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
             cx.epoch_group(a, l, ph, E, flags, tt, sn);
           } else {
             // the tile is in the layout before the PERM that ends the epoch
-            cx.func(a, l, sl);
+            cx.func(a, l, sl, (flags & kEpochNoX) != 0);
             cx.epoch_group(a, l, ph, E, flags, tt, sn);
-            if (flags) {
+            if (flags & (kEpochLoop | kEpochPhaseA | kEpochCza)) {
               if (flags & kEpochCza) cx.cza(a, l, ph, cld(&E->cza), cx.tlog | cur.y);
               if (flags & kEpochPhaseA)
                 for (int p = cld(&E->pha_first), pe = p + cld(&E->pha_count); p < pe; ++p)

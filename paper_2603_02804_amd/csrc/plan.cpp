@@ -322,6 +322,16 @@ static void fuse_epochs(Schedule* Sp) {
   // A forward epoch and its mirror share their run group, and with it the table row: a
   // run has a coefficient ref of its own.
   std::map<int, int> tab_of;
+  std::vector<char> no_x_sh(S.n_coef_shared), no_x_ps(S.n_coef_ps);
+  for (const RunRec& r : S.runs) {
+    bool ok = true, rz = false;
+    for (int i = 0; i < r.gate_count; ++i) {
+      const int kind = S.gates[S.run_gates[r.gate_begin + i]].kind;
+      rz = rz || kind == QF_RZ;
+      ok = ok && (kind == QF_RZ || (kind == QF_RY && !rz));
+    }
+    (r.coef >= 0 ? no_x_sh[r.coef] : no_x_ps[-1 - r.coef]) = ok;
+  }
   auto complete = [&](EpochRec* e, int layout) {
     for (int j = 0; j < S.R; ++j) {
       e->lds_from[j] = S.layouts[e->perm_from >= 0 ? e->perm_from : e->perm_to].lds_reg[j];
@@ -333,14 +343,16 @@ static void fuse_epochs(Schedule* Sp) {
     std::memset(&t, 0, sizeof(t));
     for (int j = 0; j < kMaxR; ++j) t.ref[j] = INT32_MIN;
     int n = 0;
+    bool no_x = true;
     for (int j = 0; j < S.R; ++j)
       if ((e->ry_b >> j) & 1) {
         const int ref = S.rygs[e->ry_a + n++].ref;
+        no_x = no_x && (ref >= 0 ? no_x_sh[ref] : no_x_ps[-1 - ref]);
         e->ref[j] = ref;
         if (ref >= 0) t.ref[j] = ref;
         else e->ps_mask |= 1 << j;
       }
-    e->flags = (e->perm_from < 0 ? kEpochStay : 0) | (e->ps_mask ? kEpochPs : 0) | (e->czg_loop | e->pev_loop ? kEpochLoop : 0) |
+    e->flags = (e->perm_from < 0 ? kEpochStay : 0) | (no_x ? kEpochNoX : 0) | (e->ps_mask ? kEpochPs : 0) | (e->czg_loop | e->pev_loop ? kEpochLoop : 0) |
                (e->pha_count > 0 ? kEpochPhaseA : 0) | (e->cza >= 0 ? kEpochCza : 0);
     const int key = S.rygs[e->ry_a].ref;
     auto f = tab_of.find(key);

@@ -149,7 +149,11 @@ struct PhaEntry {
 // stands.  What the kernels
 // need of other tables is repeated here, so that an epoch's scalar reads depend on
 // its index alone and not on one another.
-enum EpochFlags : int32_t { kEpochPs = 1, kEpochLoop = 2, kEpochPhaseA = 4, kEpochCza = 8, kEpochStay = 16 };
+// kEpochNoX: every run of the group is RY gates followed by RZ gates.  Their generators
+// have no X part at the cut after the run's RY, so the adjoint leaves that functional out.
+enum EpochFlags : int32_t {
+  kEpochPs = 1, kEpochLoop = 2, kEpochPhaseA = 4, kEpochCza = 8, kEpochStay = 16, kEpochNoX = 32
+};
 struct EpochRec {
   // one cache line: all that an epoch without any of the flagged sub-ops reads
   uint32_t lds_from[kMaxR], lds_to[kMaxR];             // lds_reg of the two layouts
