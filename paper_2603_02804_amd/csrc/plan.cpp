@@ -770,6 +770,18 @@ static bool build_with_fill(const Circuit& C, const Tuning& T, Schedule* Sp, std
       // wires whose items are all applied first (no per-amplitude work), then priority
       cands = by_priority(cands);
       std::stable_sort(cands.begin(), cands.end(), [&](int a, int b) { return gap_clear(a) > gap_clear(b); });
+      // The pass loads its tile straight into this layout, and the adjoint pass stores from
+      // it: wires at the lowest memory bits stay out of the registers if others are as
+      // ready, so that 16 lanes read and write 128 contiguous bytes.  (The first pass of a
+      // circuit with input angles starts from |0...0> and reads nothing.)
+      auto high_first = [&](std::vector<int>* qs) {
+        std::stable_sort(qs->begin(), qs->end(), [&](int a, int b) {
+          if (gap_clear(a) != gap_clear(b)) return gap_clear(a) > gap_clear(b);
+          return (pos_of[a] >= ncore) > (pos_of[b] >= ncore);
+        });
+      };
+      const bool reads = at_load && (pass_id > 0 || S.n_coef_ps == 0);
+      if (reads) high_first(&cands);
       std::vector<int> want(cands.begin(), cands.begin() + std::min<size_t>(R, cands.size()));
       const int n_run_wires = (int)want.size();
       if ((int)want.size() < R) {
@@ -777,6 +789,7 @@ static bool build_with_fill(const Circuit& C, const Tuning& T, Schedule* Sp, std
         for (int q : local)
           if (std::find(want.begin(), want.end(), q) == want.end()) others.push_back(q);
         others = by_priority(others);
+        if (reads) high_first(&others);
         for (int q : others)
           if ((int)want.size() < R) want.push_back(q);
       }
@@ -850,10 +863,7 @@ static bool build_with_fill(const Circuit& C, const Tuning& T, Schedule* Sp, std
 
     std::vector<int> out_map(n);
     std::vector<int> next_local;
-    if (n <= k) {
-      out_map = in_map;
-      next_local = local;
-    } else {
+    {
       std::vector<int> pr_all = by_priority(all);
       next_local.assign(pr_all.begin(), pr_all.begin() + k);
       auto in_cur = [&](int q) { return pos_of[q] >= 0; };
@@ -874,13 +884,16 @@ static bool build_with_fill(const Circuit& C, const Tuning& T, Schedule* Sp, std
       std::vector<int> shared;
       for (int q : next_local)
         if (in_cur(q)) shared.push_back(q);
+      // the lowest memory bits of the output: the qubits at the lowest lane bits of the
+      // layout that the pass stores from, in lane order (whole lines, see the load above;
+      // with one amplitude per line and lane, 12 qubits x 100 layers x 1,024 samples took
+      // 2.68 ms per step against 2.29, and a pass of three epochs at 20 qubits, 128 samples,
+      // 619 us against 495)
       std::vector<int> core;
-      for (int r = 0; r < 4 && (int)core.size() < ncore; ++r)
+      const LayoutRec& last_layout = S.layouts[cur];
+      for (int b = 0; b < tb && (int)core.size() < ncore; ++b)
         for (int q : shared)
-          if ((pos_of[q] & 3) == r && std::find(core.begin(), core.end(), q) == core.end()) {
-            core.push_back(q);
-            break;
-          }
+          if ((last_layout.log_thr[b] >> q) & 1u) core.push_back(q);
       for (int q : shared)
         if ((int)core.size() < ncore && std::find(core.begin(), core.end(), q) == core.end()) core.push_back(q);
       int m = 0;
