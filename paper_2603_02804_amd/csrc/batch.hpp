@@ -84,6 +84,7 @@ struct CircProgram {
 // the driver is a fake base equal to the circuit's offset in the batch
 // workspace, so every workspace address it forms is that offset.
 struct RecordExec {
+  static constexpr bool kSeedsInPass = false;
   const PlanCore& c;
   const PlanPtrs& d;
   int circ;

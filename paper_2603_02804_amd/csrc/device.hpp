@@ -451,18 +451,18 @@ struct PassCtx {
   static constexpr int WAVES = NT / 64;
   KArgs A;
   float2* lds;
-  int t;
   uint32_t tlog;
   bool active;
-  int sample, lane, wave, n_slots;
+  int sample, wave, n_slots;
 
   // Entry `row * NT + t` of a per-thread table: the wave's uniform address and the lane's
-  // 32-bit offset.  The lane id is made opaque, so that no register carries a thread
-  // offset or a 64-bit address through the epoch loop (the adjoint pass would spill them).
-  __device__ __forceinline__ uint32_t lane_id() const {
-    uint32_t id = (uint32_t)lane;
-    asm volatile("" : "+v"(id));
-    return id;
+  // 32-bit offset.  The lane id is formed anew where it is used (lane_id: three
+  // instructions from an opaque zero), so that neither it nor a thread offset or a 64-bit
+  // address takes a register through the epoch loop (the adjoint pass would spill them).
+  static __device__ __forceinline__ uint32_t lane_id() {
+    uint32_t zero = 0;
+    asm volatile("" : "+v"(zero));
+    return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
   }
   template <class T>
   __device__ __forceinline__ T thread_entry(const void* tab, int row, int entry_bytes, uint32_t id) const {
@@ -481,7 +481,7 @@ struct PassCtx {
     return thread_entry<float2>(A.tab, row, sizeof(float2), id);
   }
   __device__ __forceinline__ uint32_t mem_base(int layout) const {
-    return A.tbases[(size_t)layout * NT + t].mem;
+    return thread_entry<ThrBase>(A.tbases, layout, sizeof(ThrBase), lane_id()).mem;
   }
   // logical base of `layout`, reusing the bases `cur` of layout `cur_idx` when they match
   __device__ __forceinline__ uint32_t log_base(int layout, int cur_idx, uint2 cur) const {
@@ -554,6 +554,88 @@ struct PassCtx {
     if constexpr (BWD) apply_group<R>(l, tt, sn);
   }
 
+  // The tile from memory into `layout`.  Every lane loads: the thread tables are zero above
+  // the tile's thread bits, so lanes beyond the tile read (and later drop) in-tile elements.
+  __device__ __forceinline__ void load(float2 (&v)[NA], const float* from, long long stride, bool bf16, int sl,
+                                       int layout, uint32_t tile_bits) const {
+    const uint32_t base = tile_bits | mem_base(layout);
+    RegBits<R> rb;
+    rb.load((A.layouts + layout)->mem_reg);
+    if (bf16) {
+      const uint32_t* src = reinterpret_cast<const uint32_t*>(from) + sl * stride;
+#pragma unroll
+      for (int jj = 0; jj < NA; ++jj) v[jj] = widen_bf16x2(src[base | rb(jj)]);
+    } else {
+      const float2* src = reinterpret_cast<const float2*>(from) + sl * stride;
+#pragma unroll
+      for (int jj = 0; jj < NA; ++jj) v[jj] = src[base | rb(jj)];
+    }
+  }
+
+  // Adjoint seed of general Pauli strings, lambda = 2 sum_k g_k P_k psi (App. B.2), from the
+  // stored output state that the pass loads as psi; masks in its bit order, which is also
+  // the load's.  (P psi)_y = i^ny (-1)^{popcount((y ^ xm) & zm)} psi_{y ^ xm}.  A kernel of
+  // its own wrote lambda for the pass to read: 467 us of 3.5 ms for a 20-qubit layer.
+  __device__ __forceinline__ void seed_pauli(float2 (&l)[NA], int sl, int layout, uint32_t tile_bits) const {
+    const uint32_t base = tile_bits | mem_base(layout);
+    RegBits<R> rb;
+    rb.load((A.layouts + layout)->mem_reg);
+    const float2* src = reinterpret_cast<const float2*>(A.src0) + sl * A.s0;
+    const float* g = A.dE + (size_t)sample * A.K;
+#pragma unroll
+    for (int jj = 0; jj < NA; ++jj) l[jj] = make_float2(0.f, 0.f);
+#pragma unroll 1
+    for (int k = 0; k < A.K; ++k) {
+      const uint32_t xm = cld(&A.pauli[k].xm), zm = cld(&A.pauli[k].zm);
+      const int ny = cld(&A.pauli[k].ny);
+      const float gk = cld(g + k);
+      // g i^ny
+      const float gr = (ny & 1) ? 0.f : (ny & 2) ? -gk : gk, gi = (ny & 1) ? ((ny & 2) ? -gk : gk) : 0.f;
+      float2 v[NA];
+#pragma unroll
+      for (int jj = 0; jj < NA; ++jj) v[jj] = src[(base | rb(jj)) ^ xm];
+#pragma unroll
+      for (int jj = 0; jj < NA; ++jj) {
+        const uint32_t flip = (uint32_t)__popc(((base | rb(jj)) ^ xm) & zm) << 31;
+        const float wr = __uint_as_float(__float_as_uint(gr) ^ flip), wi = __uint_as_float(__float_as_uint(gi) ^ flip);
+        l[jj].x = fmaf(wr, v[jj].x, l[jj].x);
+        l[jj].x = fmaf(-wi, v[jj].y, l[jj].x);
+        l[jj].y = fmaf(wr, v[jj].y, l[jj].y);
+        l[jj].y = fmaf(wi, v[jj].x, l[jj].y);
+      }
+    }
+#pragma unroll
+    for (int jj = 0; jj < NA; ++jj) l[jj] = make_float2(2.f * l[jj].x, 2.f * l[jj].y);
+  }
+
+  // Partial sums of the Z-string expectations over the wave.  base: the thread's logical
+  // index in `layout`.
+  __device__ __forceinline__ void expect(const float2 (&a)[NA], int item, uint32_t base, int layout) const {
+    RegBits<R> rb;
+    rb.load((A.layouts + layout)->log_reg);
+    float p[NA];
+#pragma unroll
+    for (int jj = 0; jj < NA; ++jj)   // lanes beyond a small tile hold copies of in-tile elements
+      p[jj] = active ? fmaf(a[jj].x, a[jj].x, a[jj].y * a[jj].y) : 0.f;
+    for (int k0 = 0; k0 < A.K; k0 += 16) {
+      float v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        v[k] = 0.f;
+        if (k0 + k < A.K) {
+          const uint32_t zk = cld(A.zmask + k0 + k);
+#pragma unroll
+          for (int jj = 0; jj < NA; ++jj)
+            v[k] += __uint_as_float(__float_as_uint(p[jj]) ^ ((uint32_t)__popc((base | rb(jj)) & zk) << 31));
+        }
+      }
+      const int lane = (int)lane_id();
+      const float s = wave_reduce16(v, lane);
+      const int idx = wave_sum_index(lane);
+      if (wave_sum_writer(lane) && k0 + idx < A.K) A.partE[((size_t)item * WAVES + wave) * A.K + k0 + idx] = s;
+    }
+  }
+
   // x: the thread's logical base index in the current layout
   __device__ __forceinline__ void diagt(float2 (&a)[NA], float2 (&l)[NA], float2& ph, uint32_t x, int czg0, int nczg, int pev0, int npev) const {
   uint32_t par = 0;
@@ -620,6 +702,7 @@ struct PassCtx {
   // ms per step).
   __device__ __forceinline__ void func(const float2 (&a)[NA], const float2 (&l)[NA], const int (&sl)[R],
                                        bool no_x) const {
+    const int lane = (int)lane_id();
     if constexpr (BWD) {
       // part[wave][slot][Pauli], through an LDS-typed pointer
       __attribute__((address_space(3))) float* part = (__attribute__((address_space(3))) float*)qf_pass_part;
@@ -701,7 +784,6 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
   constexpr int NA = 1 << R;
   constexpr int WAVES = NT / 64;
   const int t = threadIdx.x;
-  const int lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int tb = A.tb;
   const bool active = t < (1 << tb);
@@ -725,252 +807,203 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
     }
   }
 
-  float2 a[NA];
-  float2 l[NA];
-#pragma unroll
-  for (int j = 0; j < NA; ++j) {
-    a[j] = make_float2(0.f, 0.f);
-    l[j] = make_float2(0.f, 0.f);
-  }
   const int n_slots = A.n_slots;
   // pending per-thread phase of the diagonal gates on thread-held qubits; it
   // multiplies psi (and, in the backward, lambda as well)
   float2 ph = make_float2(1.f, 0.f);
 
-  const PassCtx<R, NT, BWD> cx{A, lds, t, tlog, active, sample, lane, wave, n_slots};
+  const PassCtx<R, NT, BWD> cx{A, lds, tlog, active, sample, wave, n_slots};
   // bases of the layout the tile is in (cur_idx: its index, -1 = not loaded)
   int cur_idx = -1;
   uint2 cur = make_uint2(0u, 0u);
 
-  // the next op record is fetched while the current one executes
-  Op next = ld_op(A.ops);
-  for (int oi = 0; oi < A.n_ops; ++oi) {
-    const Op op = next;
-    if (oi + 1 < A.n_ops) next = ld_op(A.ops + oi + 1);
-    switch (op.kind) {
-      case OP_INIT0: {
-        const LayoutRec* L = A.layouts + op.a;
-        const uint32_t base = cx.log_base(op.a, cur_idx, cur);
-        RegBits<R> rb;
-        rb.load(L->log_reg);
+  // A program is straight: the tile comes in (INIT0 / LOAD; the adjoint also LOADs or
+  // SEEDs lambda), epochs, and it goes out (STORE).  Other ops are rare (diagonal gates
+  // after the last epoch, expectations).  Interpreting all of them in one loop copied both
+  // register arrays at every op: about 130 moves each in the adjoint, a fifth of a pass of
+  // three epochs.
+  float2 a[NA];
+  float2 l[NA];
+  Op op = ld_op(A.ops);
+  if constexpr (!BWD) {
+    if (op.kind == OP_INIT0) {
+      const uint32_t base = cx.log_base(op.a, cur_idx, cur);
+      RegBits<R> rb;
+      rb.load((A.layouts + op.a)->log_reg);
 #pragma unroll
-        for (int jj = 0; jj < NA; ++jj)
-          a[jj] = make_float2((active && (base | rb(jj)) == 0u) ? 1.f : 0.f, 0.f);
-        break;
-      }
-      case OP_LOAD: {
-        const LayoutRec* L = A.layouts + op.a;
-        const uint32_t base = (op.c ? tout : tin) | cx.mem_base(op.a);
-        RegBits<R> rb;
-        rb.load(L->mem_reg);
-        // every lane loads: the thread tables are zero above the tile's thread
-        // bits, so lanes beyond the tile read (and later drop) in-tile elements;
-        // an unpredicated load keeps the register arrays in place
-        if (op.b == 0 && A.src0_bf16) {
-          const uint32_t* src = reinterpret_cast<const uint32_t*>(A.src0) + (long long)sl * A.s0;
+      for (int jj = 0; jj < NA; ++jj) a[jj] = make_float2((active && (base | rb(jj)) == 0u) ? 1.f : 0.f, 0.f);
+    } else {
+      cx.load(a, A.src0, A.s0, A.src0_bf16 != 0, sl, op.a, op.c ? tout : tin);
+    }
+  } else {
+    cx.load(a, A.src0, A.s0, A.src0_bf16 != 0, sl, op.a, op.c ? tout : tin);
+    op = ld_op(A.ops + 1);
+    if (op.kind == OP_SEED) {
+      // lambda = 2 c(x) psi, c(x) = sum_k g_k (-1)^{|x & z_k|}
+      const uint32_t base = cx.log_base(op.a, cur_idx, cur);
+      RegBits<R> rb;
+      rb.load((A.layouts + op.a)->log_reg);
+      const float* g = A.dE + (size_t)sample * A.K;
+      float c[NA];
 #pragma unroll
-          for (int jj = 0; jj < NA; ++jj) a[jj] = widen_bf16x2(src[base | rb(jj)]);
-        } else if (op.b == 0) {
-          const float2* src = reinterpret_cast<const float2*>(A.src0) + (long long)sl * A.s0;
-#pragma unroll
-          for (int jj = 0; jj < NA; ++jj) a[jj] = src[base | rb(jj)];
-        } else if constexpr (BWD) {
-          const float2* src = reinterpret_cast<const float2*>(A.src1) + (long long)sl * A.s1;
-#pragma unroll
-          for (int jj = 0; jj < NA; ++jj) l[jj] = src[base | rb(jj)];
-        }
-        break;
-      }
-      case OP_STORE: {
-        cx.flush(a, l, ph);
-        const LayoutRec* L = A.layouts + op.a;
-        const uint32_t base = (op.c ? tout : tin) | cx.mem_base(op.a);
-        RegBits<R> rb;
-        rb.load(L->mem_reg);
-        if (active && A.dst) {
-          float2* dst = reinterpret_cast<float2*>(A.dst) + (long long)sl * A.sd;
-          if constexpr (BWD) {
-            if (A.dpsi) {
-              // also psi, un-applied to the pass input, in the same memory order
-              float2* dp = reinterpret_cast<float2*>(A.dpsi) + (long long)sl * A.sdp;
-#pragma unroll
-              for (int jj = 0; jj < NA; ++jj) {
-                const uint32_t i = base | rb(jj);
-                dst[i] = l[jj];
-                dp[i] = a[jj];
-              }
-            } else {
-#pragma unroll
-              for (int jj = 0; jj < NA; ++jj) dst[base | rb(jj)] = l[jj];
-            }
-          } else {
-#pragma unroll
-            for (int jj = 0; jj < NA; ++jj) dst[base | rb(jj)] = a[jj];
-            if (A.dst2) {
-              uint32_t* dst2 = A.dst2 + (long long)sl * A.sd2;
-#pragma unroll
-              for (int jj = 0; jj < NA; ++jj) dst2[base | rb(jj)] = pack_bf16x2(a[jj]);
-            }
-          }
-        }
-        break;
-      }
-      case OP_PERM: {
-        const uint32_t bf = op.a == cur_idx ? cur.x : cx.base2(op.a).x;
-        cur = cx.base2(op.b);
-        cur_idx = op.b;
-        RegBits<R> rf, rt;
-        rf.load((A.layouts + op.a)->lds_reg);
-        rt.load((A.layouts + op.b)->lds_reg);
-        cx.perm(a, l, ph, rf, rt, bf, cur.x);
-        break;
-      }
-      case OP_DIAGT:
-        cx.diagt(a, l, ph, cx.log_base(op.a, cur_idx, cur), op.b, op.c, op.d, op.e);
-        break;
-      case OP_CZA:
-        cx.cza(a, l, ph, op.a, cx.log_base(op.b, cur_idx, cur));
-        break;
-      case OP_PHASEA:
-        cx.phasea(a, l, op.a, op.c);
-        break;
-      case OP_EPOCH: {
-        // a run of consecutive register epochs, one iteration each, with the
-        // sub-steps of an epoch in program order; every epoch applies its run group
-        // (absent bits: t = 0, the identity), so the loop body has one path.
-        // What an epoch reads has addresses that follow from its index: its thread
-        // entries are requested one epoch ahead, its record and coefficients are
-        // brought into the scalar cache one epoch ahead.  (One sample of 10 qubits is one
-        // wave on the device: each epoch waited for a chain of four reads.  Forward passes
-        // 57 -> 46 us per launch; 12 qubits x 100 layers x 1,024 samples 2.95 -> 2.83 ms;
-        // no change at 20 qubits, where other waves hide the reads.)
-        constexpr int kStep = BWD ? -1 : 1;
-        if (op.e != cur_idx) cur = cx.base2(op.e);
-        uint2 nb_next = cx.base2(op.d);
-        float2 owed_next = cx.owes(op.c, cx.lane_id());
-        if constexpr (BWD) cmul_in(ph, make_float2(owed_next.x, -owed_next.y));
-        for (int i = 0; i < op.b; ++i) {
-          const EpochRec* E = A.epochs + op.a + i;
-          RegBits<R> rf, rt;
-          rf.load(E->lds_from);
-          rt.load(E->lds_to);
-          int sl[R];
-#pragma unroll
-          for (int j = 0; j < R; ++j) sl[j] = BWD ? cld(&E->slot[j]) : 0;
-          const int flags = cld(&E->flags);
-          const float* row = A.tco + (size_t)(op.c + kStep * i) * kTabCoefs;
-          float tt[R], sn[R];
-#pragma unroll
-          for (int j = 0; j < R; ++j) {
-            tt[j] = cld(row + j);
-            sn[j] = kScaledRot<R> ? 0.f : cld(row + 8 + j);
-          }
-          // nb: the thread's bases after the exchange; owed: what it owes when this epoch's
-          // exchange sends its amplitudes, one table entry in place of the epoch's
-          // diagonal items and scale factors
-          const uint2 nb = nb_next;
-          [[maybe_unused]] const float2 owed = owed_next;
-          const int in = min(i + 1, op.b - 1);   // (the last epoch reads its own again)
-          const uint32_t id = cx.lane_id();
-          nb_next = cx.base2(op.d + kStep * in, id);
-          owed_next = cx.owes(op.c + kStep * in, id);
-          const int warm = cld(&(A.epochs + op.a + in)->flags) ^
-                           __float_as_int(cld(A.tco + (size_t)(op.c + kStep * in) * kTabCoefs));
-          asm volatile("" ::"s"(warm));
-          if constexpr (!BWD) {
-            if (flags & kEpochStay) cx.flush(a, l, ph);
-            else cx.perm(a, l, ph, rf, rt, cur.x, nb.x);
-            cur = nb;
-            ph = owed;
-            if (flags & (kEpochLoop | kEpochPhaseA | kEpochCza)) {
-              if (flags & kEpochLoop)
-                cx.diagt(a, l, ph, cx.tlog | cur.y, cld(&E->czg_first), cld(&E->czg_loop), cld(&E->pev_first),
-                         cld(&E->pev_loop));
-              if (flags & kEpochPhaseA)
-                for (int p = cld(&E->pha_first), pe = p + cld(&E->pha_count); p < pe; ++p)
-                  cx.phasea(a, l, cld(&A.phas[p].regbit), cld(&A.phas[p].ref));
-              if (flags & kEpochCza) cx.cza(a, l, ph, cld(&E->cza), cx.tlog | cur.y);
-            }
-            cx.epoch_group(a, l, ph, E, flags, tt, sn);
-          } else {
-            // the tile is in the layout before the PERM that ends the epoch
-            cx.func(a, l, sl, (flags & kEpochNoX) != 0);
-            cx.epoch_group(a, l, ph, E, flags, tt, sn);
-            if (flags & (kEpochLoop | kEpochPhaseA | kEpochCza)) {
-              if (flags & kEpochCza) cx.cza(a, l, ph, cld(&E->cza), cx.tlog | cur.y);
-              if (flags & kEpochPhaseA)
-                for (int p = cld(&E->pha_first), pe = p + cld(&E->pha_count); p < pe; ++p)
-                  cx.phasea(a, l, cld(&A.phas[p].regbit), cld(&A.phas[p].ref));
-              if (flags & kEpochLoop)
-                cx.diagt(a, l, ph, cx.tlog | cur.y, cld(&E->czg_first), cld(&E->czg_loop), cld(&E->pev_first),
-                         cld(&E->pev_loop));
-            }
-            // (kEpochStay: an exchange with itself, once per pass; a branch around it
-            // made the compiler spill, 8% at 20 qubits)
-            cx.perm(a, l, ph, rf, rt, cur.x, nb.x);
-            cur = nb;
-            ph = make_float2(owed_next.x, -owed_next.y);
-          }
-        }
-        if constexpr (BWD) ph = make_float2(1.f, 0.f);   // (the last epoch's owed factor once more)
-        cur_idx = op.d + kStep * (op.b - 1);
-        break;
-      }
-      case OP_EXPECT: {
-        if constexpr (!BWD) {
-          if (!A.do_expect) break;
-          // the pending factor may hold scale factors
-          cx.flush(a, l, ph);
-          const LayoutRec* L = A.layouts + op.a;
-          const uint32_t base = cx.log_base(op.a, cur_idx, cur);
-          RegBits<R> rb;
-          rb.load(L->log_reg);
-          for (int k0 = 0; k0 < A.K; k0 += 16) {
-            float v[16];
-#pragma unroll
-            for (int k = 0; k < 16; ++k) v[k] = 0.f;
-#pragma unroll
-            for (int jj = 0; jj < NA; ++jj) {
-              const uint32_t x = base | rb(jj);
-              // lanes beyond a small tile hold copies of in-tile elements
-              const float p = active ? fmaf(a[jj].x, a[jj].x, a[jj].y * a[jj].y) : 0.f;
-#pragma unroll
-              for (int k = 0; k < 16; ++k)
-                if (k0 + k < A.K) v[k] += (__popc(x & cld(A.zmask + k0 + k)) & 1) ? -p : p;
-            }
-            const float s = wave_reduce16(v, lane);
-            const int idx = wave_sum_index(lane);
-            if (wave_sum_writer(lane) && k0 + idx < A.K)
-              A.partE[((size_t)item * WAVES + wave) * A.K + k0 + idx] = s;
-          }
-        }
-        break;
-      }
-      case OP_SEED: {
-        if constexpr (BWD) {
-          const LayoutRec* L = A.layouts + op.a;
-          const uint32_t base = cx.log_base(op.a, cur_idx, cur);
-          RegBits<R> rb;
-          rb.load(L->log_reg);
-          const float* g = A.dE + (size_t)sample * A.K;
-          // lambda = 2 c(x) psi, c(x) = sum_k g_k (-1)^{|x & z_k|}
-          float c[NA];
-#pragma unroll
-          for (int jj = 0; jj < NA; ++jj) c[jj] = 0.f;
+      for (int jj = 0; jj < NA; ++jj) c[jj] = 0.f;
 #pragma unroll 1
-          for (int k = 0; k < A.K; ++k) {
-            const float gk = cld(g + k);
-            const uint32_t zk = cld(A.zmask + k);
+      for (int k = 0; k < A.K; ++k) {
+        const float gk = cld(g + k);
+        const uint32_t zk = cld(A.zmask + k);
 #pragma unroll
-            for (int jj = 0; jj < NA; ++jj) c[jj] += (__popc((base | rb(jj)) & zk) & 1) ? -gk : gk;
-          }
-#pragma unroll
-          for (int jj = 0; jj < NA; ++jj) l[jj] = make_float2(2.f * c[jj] * a[jj].x, 2.f * c[jj] * a[jj].y);
-        }
-        break;
+        for (int jj = 0; jj < NA; ++jj) c[jj] += (__popc((base | rb(jj)) & zk) & 1) ? -gk : gk;
       }
-      default:
-        break;
+#pragma unroll
+      for (int jj = 0; jj < NA; ++jj) l[jj] = make_float2(2.f * c[jj] * a[jj].x, 2.f * c[jj] * a[jj].y);
+    } else if (A.pauli) {
+      cx.seed_pauli(l, sl, op.a, op.c ? tout : tin);
+    } else {
+      cx.load(l, A.src1, A.s1, false, sl, op.a, op.c ? tout : tin);
+    }
+  }
+  int oi = BWD ? 2 : 1;
+  op.kind = 0;
+  while (true) {
+    for (; oi < A.n_ops; ++oi) {
+      op = ld_op(A.ops + oi);
+      if (op.kind == OP_EPOCH || op.kind == OP_STORE) break;
+      switch (op.kind) {
+        case OP_DIAGT:
+          cx.diagt(a, l, ph, cx.log_base(op.a, cur_idx, cur), op.b, op.c, op.d, op.e);
+          break;
+        case OP_CZA:
+          cx.cza(a, l, ph, op.a, cx.log_base(op.b, cur_idx, cur));
+          break;
+        case OP_PHASEA:
+          cx.phasea(a, l, op.a, op.c);
+          break;
+        case OP_EXPECT:
+          if constexpr (!BWD) {
+            // (the pending factor may hold scale factors)
+            if (A.do_expect) {
+              cx.flush(a, l, ph);
+              cx.expect(a, item, cx.log_base(op.a, cur_idx, cur), op.a);
+            }
+          }
+          break;
+        default:
+          break;
+      }
+    }
+    if (oi >= A.n_ops || op.kind != OP_EPOCH) break;
+    ++oi;
+    // a run of consecutive register epochs, one iteration each, with the
+    // sub-steps of an epoch in program order; every epoch applies its run group
+    // (absent bits: t = 0, the identity), so the loop body has one path.
+    // What an epoch reads has addresses that follow from its index: its thread
+    // entries are requested one epoch ahead, its record and coefficients are
+    // brought into the scalar cache one epoch ahead.  (One sample of 10 qubits is one
+    // wave on the device: each epoch waited for a chain of four reads.  Forward passes
+    // 57 -> 46 us per launch; 12 qubits x 100 layers x 1,024 samples 2.95 -> 2.83 ms;
+    // no change at 20 qubits, where other waves hide the reads.)
+    constexpr int kStep = BWD ? -1 : 1;
+    if (op.e != cur_idx) cur = cx.base2(op.e);
+    uint2 nb_next = cx.base2(op.d);
+    float2 owed_next = cx.owes(op.c, cx.lane_id());
+    if constexpr (BWD) cmul_in(ph, make_float2(owed_next.x, -owed_next.y));
+    for (int i = 0; i < op.b; ++i) {
+      const EpochRec* E = A.epochs + op.a + i;
+      RegBits<R> rf, rt;
+      rf.load(E->lds_from);
+      rt.load(E->lds_to);
+      int sl[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) sl[j] = BWD ? cld(&E->slot[j]) : 0;
+      const int flags = cld(&E->flags);
+      const float* row = A.tco + (size_t)(op.c + kStep * i) * kTabCoefs;
+      float tt[R], sn[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        tt[j] = cld(row + j);
+        sn[j] = kScaledRot<R> ? 0.f : cld(row + 8 + j);
+      }
+      // nb: the thread's bases after the exchange; owed: what it owes when this epoch's
+      // exchange sends its amplitudes, one table entry in place of the epoch's
+      // diagonal items and scale factors
+      const uint2 nb = nb_next;
+      [[maybe_unused]] const float2 owed = owed_next;
+      const int in = min(i + 1, op.b - 1);   // (the last epoch reads its own again)
+      const uint32_t id = cx.lane_id();
+      nb_next = cx.base2(op.d + kStep * in, id);
+      owed_next = cx.owes(op.c + kStep * in, id);
+      const int warm = cld(&(A.epochs + op.a + in)->flags) ^
+                       __float_as_int(cld(A.tco + (size_t)(op.c + kStep * in) * kTabCoefs));
+      asm volatile("" ::"s"(warm));
+      if constexpr (!BWD) {
+        if (flags & kEpochStay) cx.flush(a, l, ph);
+        else cx.perm(a, l, ph, rf, rt, cur.x, nb.x);
+        cur = nb;
+        ph = owed;
+        if (flags & (kEpochLoop | kEpochPhaseA | kEpochCza)) {
+          if (flags & kEpochLoop)
+            cx.diagt(a, l, ph, cx.tlog | cur.y, cld(&E->czg_first), cld(&E->czg_loop), cld(&E->pev_first),
+                     cld(&E->pev_loop));
+          if (flags & kEpochPhaseA)
+            for (int p = cld(&E->pha_first), pe = p + cld(&E->pha_count); p < pe; ++p)
+              cx.phasea(a, l, cld(&A.phas[p].regbit), cld(&A.phas[p].ref));
+          if (flags & kEpochCza) cx.cza(a, l, ph, cld(&E->cza), cx.tlog | cur.y);
+        }
+        cx.epoch_group(a, l, ph, E, flags, tt, sn);
+      } else {
+        // the tile is in the layout before the PERM that ends the epoch
+        cx.func(a, l, sl, (flags & kEpochNoX) != 0);
+        cx.epoch_group(a, l, ph, E, flags, tt, sn);
+        if (flags & (kEpochLoop | kEpochPhaseA | kEpochCza)) {
+          if (flags & kEpochCza) cx.cza(a, l, ph, cld(&E->cza), cx.tlog | cur.y);
+          if (flags & kEpochPhaseA)
+            for (int p = cld(&E->pha_first), pe = p + cld(&E->pha_count); p < pe; ++p)
+              cx.phasea(a, l, cld(&A.phas[p].regbit), cld(&A.phas[p].ref));
+          if (flags & kEpochLoop)
+            cx.diagt(a, l, ph, cx.tlog | cur.y, cld(&E->czg_first), cld(&E->czg_loop), cld(&E->pev_first),
+                     cld(&E->pev_loop));
+        }
+        // (kEpochStay: an exchange with itself, once per pass; a branch around it
+        // made the compiler spill, 8% at 20 qubits)
+        cx.perm(a, l, ph, rf, rt, cur.x, nb.x);
+        cur = nb;
+        ph = make_float2(owed_next.x, -owed_next.y);
+      }
+    }
+    if constexpr (BWD) ph = make_float2(1.f, 0.f);   // (the last epoch's owed factor once more)
+    cur_idx = op.d + kStep * (op.b - 1);
+  }
+  if (oi < A.n_ops) {   // STORE
+    cx.flush(a, l, ph);
+    const LayoutRec* L = A.layouts + op.a;
+    const uint32_t base = (op.c ? tout : tin) | cx.mem_base(op.a);
+    RegBits<R> rb;
+    rb.load(L->mem_reg);
+    if (active && A.dst) {
+      float2* dst = reinterpret_cast<float2*>(A.dst) + (long long)sl * A.sd;
+      if constexpr (BWD) {
+        if (A.dpsi) {
+          // also psi, un-applied to the pass input, in the same memory order
+          float2* dp = reinterpret_cast<float2*>(A.dpsi) + (long long)sl * A.sdp;
+#pragma unroll
+          for (int jj = 0; jj < NA; ++jj) {
+            const uint32_t i = base | rb(jj);
+            dst[i] = l[jj];
+            dp[i] = a[jj];
+          }
+        } else {
+#pragma unroll
+          for (int jj = 0; jj < NA; ++jj) dst[base | rb(jj)] = l[jj];
+        }
+      } else {
+#pragma unroll
+        for (int jj = 0; jj < NA; ++jj) dst[base | rb(jj)] = a[jj];
+        if (A.dst2) {
+          uint32_t* dst2 = A.dst2 + (long long)sl * A.sd2;
+#pragma unroll
+          for (int jj = 0; jj < NA; ++jj) dst2[base | rb(jj)] = pack_bf16x2(a[jj]);
+        }
+      }
     }
   }
   if constexpr (BWD) {
@@ -978,7 +1011,7 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
     if (n_slots > 0) {
       __syncthreads();
       const float* part = qf_pass_part;
-      for (int i = t; i < 3 * n_slots; i += NT) {
+      for (int i = wave * 64 + (int)cx.lane_id(); i < 3 * n_slots; i += NT) {
         float acc = 0.f;
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) acc += part[w * 3 * n_slots + i];

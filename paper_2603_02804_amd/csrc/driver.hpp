@@ -40,6 +40,7 @@ struct PassLaunch {
   float* partE = nullptr;   // forward expectation partial sums
   const float* dE = nullptr;
   int do_expect = 0;
+  bool seed_pauli = false;  // backward: the pass seeds lambda from psi (X / Y observables)
   bool load_input = false;  // pass 0 reads a caller's initial state from src0
 };
 
@@ -467,9 +468,11 @@ qf_status run_backward_fused(const PlanCore& c, Exec& ex, const float* theta, co
         if (p == b - 1) { L.src0 = ck + s * SA; L.src0_stride = ck_stride; }
         else if (c.uncompute) { L.src0 = work + (p & 1) * SA * nb; L.src0_stride = SA; }
         else { L.src0 = seg + int64_t(p - a) * SS; L.src0_stride = SS * (c.ckpt - 1); L.src0_bf16 = bf; }
-        if (p == c.P - 1 && c.S.general_obs)   // seed from the stored output state
+        // the last pass: lambda from the stored output state, by the pass itself if it can
+        L.seed_pauli = Exec::kSeedsInPass && p == c.P - 1 && c.S.general_obs;
+        if (p == c.P - 1 && c.S.general_obs && !L.seed_pauli)
           ex.pauli_seed((const float*)(ck + s * SA), ck_stride, lam + li * SA * nb, SA, nb, mb0, dE);
-        if (p != c.P - 1 || c.S.general_obs) { L.src1 = lam + li * SA * nb; L.src1_stride = SA; }
+        if (p != c.P - 1 || (c.S.general_obs && !L.seed_pauli)) { L.src1 = lam + li * SA * nb; L.src1_stride = SA; }
         if (p > 0) { L.dst = lam + (1 - li) * SA * nb; L.dst_stride = SA; }
         if (c.uncompute && p > a) { L.dpsi = work + ((p - 1) & 1) * SA * nb; L.dpsi_stride = SA; }
         L.partF = partF + int64_t(nb) * c.partF_off[p];

@@ -76,6 +76,7 @@ struct KArgs {
   float* partE;
   const float* dE;
   const uint32_t* zmask;
+  const PauliRec* pauli;      // backward: lambda is seeded from psi and these, or null
   long long s0, s1, sd;       // per-sample strides (complex elements)
   int n_ops;
   int n_ps;                   // per-sample run coefficient rows per sample
@@ -157,6 +158,7 @@ inline KArgs make_pass_args(const PlanCore& c, const PlanPtrs& d, const CoefPtrs
   A.partE = L.partE;
   A.dE = L.dE;
   A.zmask = d.zmask;
+  A.pauli = L.seed_pauli ? d.pauli : nullptr;
   A.K = c.C.K;
   A.sample0 = L.sample0;
   A.tiles_log2 = S.tiles_log2;

@@ -991,6 +991,11 @@ static bool build_with_fill(const Circuit& C, const Tuning& T, Schedule* Sp, std
     p0.fload_begin = (int)S.ops.size();
     S.ops.insert(S.ops.end(), f.begin(), f.end());
   }
+  for (const Op& o : S.ops)
+    if (o.kind == OP_PERM || o.kind == OP_RY || o.kind == OP_RYG || o.kind == OP_FUNC) {
+      if (msg) *msg = "scheduler left a run group or an exchange outside the epochs";
+      return false;
+    }
   if (runs_left != 0) {
     if (msg) *msg = "scheduler left runs unapplied";
     return false;

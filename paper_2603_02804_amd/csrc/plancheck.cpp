@@ -88,6 +88,7 @@ inline CF cmul(float ar, float ai, CF b) { return {ar * b.re - ai * b.im, ar * b
 [[noreturn]] void oob(const char* what) { throw std::runtime_error(std::string("out of bounds: ") + what); }
 
 struct CpuExec {
+  static constexpr bool kSeedsInPass = false;
   const PlanCore& c;
   const char* ws_lo = nullptr;   // workspace range every state / partial access must stay in
   const char* ws_hi = nullptr;

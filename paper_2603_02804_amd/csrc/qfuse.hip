@@ -333,6 +333,7 @@ static PassFn select_pass(int R, int NT, bool bwd) {
 bool have_pass_kernel(int R, int NT) { return select_pass(R, NT, false) != nullptr; }
 
 struct GpuExec {
+  static constexpr bool kSeedsInPass = true;
   const PlanCore& c;
   const DevPlan& d;
   hipStream_t st;
