@@ -85,6 +85,7 @@ struct CircProgram {
 // workspace, so every workspace address it forms is that offset.
 struct RecordExec {
   static constexpr bool kSeedsInPass = false;
+  static constexpr bool kDirectE = false;
   const PlanCore& c;
   const PlanPtrs& d;
   int circ;

@@ -352,10 +352,9 @@ qf_status run_backward_pg(const PlanCore& c, Exec& ex, const Real* theta, const 
 template <class Exec>
 std::pair<const float*, int64_t> forward_passes(const PlanCore& c, Exec& ex, char* ws, int mb0, int nb,
                                                 bool keep_ckpt, float* ckpt_base, bool do_expect,
-                                                const float* psi0) {
+                                                const float* psi0, float* partE) {
   const int64_t SA = 2 * c.amps;   // floats per state
   float* work = at<float>(ws, c.off_work);
-  float* partE = at<float>(ws, c.off_partE);
   const float* src = nullptr;
   int64_t src_stride = 0;
   for (int p = 0; p < c.P; ++p) {
@@ -396,12 +395,15 @@ qf_status run_forward_fused(const PlanCore& c, Exec& ex, const float* theta, con
   for (int mb0 = 0; mb0 < c.B; mb0 += c.mb) {
     const int nb = std::min(c.mb, c.B - mb0);
     float* ck = at<float>(ws, c.off_ckpt) + (c.store ? int64_t(mb0) * c.n_seg * SA : 0);
-    const auto fin = forward_passes(c, ex, ws, mb0, nb, c.store != 0, ck, true, psi0);
+    // one partial sum per expectation (a tile of one wave): it is the expectation
+    const bool direct = Exec::kDirectE && c.tiles * c.waves == 1 && !c.S.general_obs;
+    const auto fin = forward_passes(c, ex, ws, mb0, nb, c.store != 0, ck, true, psi0,
+                                    direct ? E + int64_t(mb0) * c.C.K : at<float>(ws, c.off_partE));
     if (c.S.general_obs) {
       // X / Y observables: from the stored output state, in its bit order
       ex.pauli_expect(fin.first, fin.second, nb, at<float>(ws, c.off_partE));
       ex.pauli_reduce_E(nb, mb0, (const float*)at<float>(ws, c.off_partE), E);
-    } else {
+    } else if (!direct) {
       ex.reduce_E(nb, mb0, at<float>(ws, c.off_partE), E);
     }
   }
@@ -422,7 +424,7 @@ qf_status run_backward_fused(const PlanCore& c, Exec& ex, const float* theta, co
   for (int mb0 = 0; mb0 < c.B; mb0 += c.mb) {
     const int nb = std::min(c.mb, c.B - mb0);
     float* ck = at<float>(ws, c.off_ckpt) + (c.store ? int64_t(mb0) * c.n_seg * SA : 0);
-    if (!c.store) forward_passes(c, ex, ws, mb0, nb, true, ck, false, psi0);
+    if (!c.store) forward_passes(c, ex, ws, mb0, nb, true, ck, false, psi0, at<float>(ws, c.off_partE));
     const int64_t ck_stride = SA * c.n_seg;
     int li = 0;
     for (int s = c.n_seg - 1; s >= 0; --s) {

@@ -90,6 +90,7 @@ inline qf_status upload_plan(const PlanCore& c, DevPlan* d, std::string* msg) {
   push_table(blob, o, c.ps_pass);        // 30
   push_table(blob, o, c.ps_begin);       // 31
   push_table(blob, o, c.ps_runs);        // 32
+  push_table(blob, o, c.S.tevs);         // 33
   d->bytes = blob.size();
   if (hipMalloc(&d->blob, d->bytes) != hipSuccess) {
     if (msg) *msg = "hipMalloc of plan tables failed";
@@ -136,6 +137,7 @@ inline qf_status upload_plan(const PlanCore& c, DevPlan* d, std::string* msg) {
   t.consts = (const double*)(b + o[27]);
   p.tbases = (const ThrBase*)(b + o[28]);
   p.trecs = (const TabRec*)(b + o[29]);
+  p.tevs = (const TabEvent*)(b + o[33]);
   return QF_OK;
 }
 

@@ -48,7 +48,8 @@ struct PlanPtrs {
   const CzaRec* cza = nullptr;
   const PauliRec* pauli = nullptr;   // observables in the final state's bit order
   const ThrBase* tbases = nullptr;   // [layout][thread] bases (S.NT threads per layout)
-  const TabRec* trecs = nullptr;     // epoch table rows
+  const TabRec* trecs = nullptr;     // epoch table rows and their phase events
+  const TabEvent* tevs = nullptr;
   Tabs tabs{};
 };
 

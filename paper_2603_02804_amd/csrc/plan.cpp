@@ -361,8 +361,12 @@ static void fuse_epochs(Schedule* Sp) {
       return;
     }
     t.layout = layout;
-    t.pev_first = e->pev_first + e->pev_loop;
-    t.pev_count = e->pev_count - e->pev_loop;
+    t.tev_first = (int)S.tevs.size();
+    for (int i = e->pev_loop; i < e->pev_count; ++i) {
+      const PhaseEv& p = S.pev[e->pev_first + i];
+      S.tevs.push_back({p.q, S.events[p.ref].prev_ref, S.events[p.ref].next_ref, 0});
+    }
+    t.tev_count = (int)S.tevs.size() - t.tev_first;
     t.czg_first = e->czg_first + e->czg_loop;
     t.czg_count = e->czg_count - e->czg_loop;
     t.pha_first = e->pha_first;

@@ -66,7 +66,8 @@ struct Schedule {
   std::vector<RygEntry> rygs;
   std::vector<EpochRec> epochs;
   std::vector<PhaEntry> phas;
-  std::vector<TabRec> tabs;           // epoch table rows
+  std::vector<TabRec> tabs;           // epoch table rows and their phase events
+  std::vector<TabEvent> tevs;
   std::vector<EventRec> events;       // phase event coefficient definitions
   int n_ev_shared = 0, n_ev_ps = 0;
   std::vector<PhaseEv> pev;           // phase events referenced by DIAGT / PHASEA ops

@@ -177,14 +177,18 @@ static_assert(sizeof(EpochRec) % 64 == 0, "epoch records are whole cache lines")
 // One row of the epoch tables, formed once per call by the coefficient kernels and
 // shared by all samples and tiles.  For every thread of the layout: the product of the
 // diagonal items that involve thread-held qubits and shared angles only (events
-// [pev_first, +pev_count), CZ groups [czg_first, +czg_count)) and of the scale factors
+// [tev_first, +tev_count), CZ groups [czg_first, +czg_count)) and of the scale factors
 // of the epoch's shared runs, corrected for the rounded norms of its register phases
 // (PhaEntry range).  For every register bit: the coefficients of its run.
 struct TabRec {
   int32_t layout;
-  int32_t pev_first, pev_count, czg_first, czg_count;
+  int32_t tev_first, tev_count, czg_first, czg_count;
   int32_t ref[kMaxR];                                  // shared runs (INT32_MIN: none, or per-sample)
   int32_t pha_first, pha_count;
+};
+// One of the row's phase events: its qubit and the shared runs it joins (INT32_MIN: none).
+struct TabEvent {
+  int32_t q, prev_ref, next_ref, pad;
 };
 constexpr int kTabCoefs = 16;                          // per row: t at [bit], s at [8 + bit]
 

@@ -89,6 +89,7 @@ inline CF cmul(float ar, float ai, CF b) { return {ar * b.re - ai * b.im, ar * b
 
 struct CpuExec {
   static constexpr bool kSeedsInPass = false;
+  static constexpr bool kDirectE = false;
   const PlanCore& c;
   const char* ws_lo = nullptr;   // workspace range every state / partial access must stay in
   const char* ws_hi = nullptr;

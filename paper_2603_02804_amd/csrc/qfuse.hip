@@ -377,6 +377,7 @@ bool have_pass_kernel(int R, int NT) { return select_pass(R, NT, false) != nullp
 
 struct GpuExec {
   static constexpr bool kSeedsInPass = true;
+  static constexpr bool kDirectE = true;
   const PlanCore& c;
   const DevPlan& d;
   hipStream_t st;

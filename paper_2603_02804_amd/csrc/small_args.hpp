@@ -34,7 +34,7 @@ struct EventArgs {
   Tabs T;
   const TabRec* trecs;
   const ThrBase* tbases;
-  const PhaseEv* pev;
+  const TabEvent* tevs;
   const CzGroup* czg;
   const PhaEntry* phas;
   const double* dsh;
@@ -134,7 +134,7 @@ inline EventArgs make_event_args(const PlanCore& c, const PlanPtrs& d, const Coe
   a.T = d.tabs;
   a.trecs = d.trecs;
   a.tbases = d.tbases;
-  a.pev = d.pev;
+  a.tevs = d.tevs;
   a.czg = d.czg;
   a.phas = d.phas;
   a.dsh = cp.dsh;

@@ -93,9 +93,16 @@ __device__ inline ZYZ zyz_split(const D2& V) {
   if (b0 > 1e-300) { Br = V.r[2] / b0; Bi = V.i[2] / b0; }
   o.zr = Ar * Br + Ai * Bi;        // A conj(B)
   o.zi = Ai * Br - Ar * Bi;
-  const double th = atan2(o.zi, o.zr);
+  // u = e^{i arg(z) / 2}, arg in (-pi, pi], by half angles of the unit z
   double s, c;
-  sincos(0.5 * th, &s, &c);
+  if (o.zr >= 0) {
+    c = sqrt(0.5 * (1.0 + o.zr));
+    s = o.zi / (2.0 * c);
+  } else {
+    const double m = sqrt(0.5 * (1.0 - o.zr));
+    c = fabs(o.zi) / (2.0 * m);
+    s = copysign(m, o.zi);
+  }
   o.ur = c;
   o.ui = s;
   o.vr = Ar * c + Ai * s;          // A conj(u)
@@ -227,20 +234,33 @@ __device__ inline void table_body(const EventArgs& a, int blk, int thread, doubl
     par ^= x & (x >> g.shift) & g.mask;
   }
   double wr = __popc(par) & 1 ? -1.0 : 1.0, wi = 0.0;
-  for (int i = 0; i < r->pev_count; ++i) {
-    const PhaseEv p = a.pev[r->pev_first + i];
-    const EventRec e = a.T.events[p.ref];
-    // conjugate where the event's qubit is 1
-    const double c = (x >> p.q) & 1 ? -1.0 : 1.0;
-    const int ref[2] = {e.prev_ref, e.next_ref};
+  // four events at a time: their records are read together, then their factors
+  for (int i0 = 0; i0 < r->tev_count; i0 += 4) {
+    TabEvent e[4];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      if (ref[k] == INT32_MIN) continue;
-      const double* d = a.dsh + kDshRow * (long long)ref[k] + 2 * k;
-      const double ur = d[0], ui = c * d[1];
-      const double tr = wr * ur - wi * ui;
-      wi = wr * ui + wi * ur;
-      wr = tr;
+    for (int i = 0; i < 4; ++i) e[i] = a.tevs[r->tev_first + min(i0 + i, r->tev_count - 1)];
+    double f[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool on = i0 + i < r->tev_count, u = on && e[i].prev_ref != INT32_MIN, v = on && e[i].next_ref != INT32_MIN;
+      const double* du = a.dsh + kDshRow * (long long)(u ? e[i].prev_ref : 0);
+      const double* dv = a.dsh + kDshRow * (long long)(v ? e[i].next_ref : 0) + 2;
+      f[i][0] = u ? du[0] : 1.0;
+      f[i][1] = u ? du[1] : 0.0;
+      f[i][2] = v ? dv[0] : 1.0;
+      f[i][3] = v ? dv[1] : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      // conjugate where the event's qubit is 1
+      const double c = (x >> e[i].q) & 1 ? -1.0 : 1.0;
+#pragma unroll
+      for (int k = 0; k < 4; k += 2) {
+        const double ur = f[i][k], ui = c * f[i][k + 1];
+        const double tr = wr * ur - wi * ui;
+        wi = wr * ui + wi * ur;
+        wr = tr;
+      }
     }
   }
   // (the scale itself is rounded before it turns, so that its remainder is known)
