@@ -91,6 +91,7 @@ inline qf_status upload_plan(const PlanCore& c, DevPlan* d, std::string* msg) {
   push_table(blob, o, c.ps_begin);       // 31
   push_table(blob, o, c.ps_runs);        // 32
   push_table(blob, o, c.S.tevs);         // 33
+  push_table(blob, o, c.S.tcor);         // 34
   d->bytes = blob.size();
   if (hipMalloc(&d->blob, d->bytes) != hipSuccess) {
     if (msg) *msg = "hipMalloc of plan tables failed";
@@ -138,6 +139,7 @@ inline qf_status upload_plan(const PlanCore& c, DevPlan* d, std::string* msg) {
   p.tbases = (const ThrBase*)(b + o[28]);
   p.trecs = (const TabRec*)(b + o[29]);
   p.tevs = (const TabEvent*)(b + o[33]);
+  p.tcor = (const int32_t*)(b + o[34]);
   return QF_OK;
 }
 

@@ -50,6 +50,7 @@ struct PlanPtrs {
   const ThrBase* tbases = nullptr;   // [layout][thread] bases (S.NT threads per layout)
   const TabRec* trecs = nullptr;     // epoch table rows and their phase events
   const TabEvent* tevs = nullptr;
+  const int32_t* tcor = nullptr;
   Tabs tabs{};
 };
 

@@ -369,8 +369,12 @@ static void fuse_epochs(Schedule* Sp) {
     t.tev_count = (int)S.tevs.size() - t.tev_first;
     t.czg_first = e->czg_first + e->czg_loop;
     t.czg_count = e->czg_count - e->czg_loop;
-    t.pha_first = e->pha_first;
-    t.pha_count = e->pha_count;
+    t.cor_first = (int)S.tcor.size();
+    for (int i = 0; i < e->pha_count; ++i)
+      if (S.phas[e->pha_first + i].ref >= 0) S.tcor.push_back(S.phas[e->pha_first + i].ref);
+    for (int i = 0; i < e->pev_loop; ++i)
+      if (S.pev[e->pev_first + i].ref >= 0) S.tcor.push_back(S.pev[e->pev_first + i].ref);
+    t.cor_count = (int)S.tcor.size() - t.cor_first;
     e->tab = tab_of[key] = (int)S.tabs.size();
     S.tabs.push_back(t);
   };

@@ -68,6 +68,7 @@ struct Schedule {
   std::vector<PhaEntry> phas;
   std::vector<TabRec> tabs;           // epoch table rows and their phase events
   std::vector<TabEvent> tevs;
+  std::vector<int32_t> tcor;          // their corrected events
   std::vector<EventRec> events;       // phase event coefficient definitions
   int n_ev_shared = 0, n_ev_ps = 0;
   std::vector<PhaseEv> pev;           // phase events referenced by DIAGT / PHASEA ops

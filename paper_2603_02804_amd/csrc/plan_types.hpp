@@ -178,13 +178,13 @@ static_assert(sizeof(EpochRec) % 64 == 0, "epoch records are whole cache lines")
 // shared by all samples and tiles.  For every thread of the layout: the product of the
 // diagonal items that involve thread-held qubits and shared angles only (events
 // [tev_first, +tev_count), CZ groups [czg_first, +czg_count)) and of the scale factors
-// of the epoch's shared runs, corrected for the rounded norms of its register phases
-// (PhaEntry range).  For every register bit: the coefficients of its run.
+// of the epoch's shared runs, corrected for the rounded norms of the shared phases that the
+// pass kernel applies itself (on register-held qubits, or on qubits outside the tile).  For every register bit: the coefficients of its run.
 struct TabRec {
   int32_t layout;
   int32_t tev_first, tev_count, czg_first, czg_count;
   int32_t ref[kMaxR];                                  // shared runs (INT32_MIN: none, or per-sample)
-  int32_t pha_first, pha_count;
+  int32_t cor_first, cor_count;                        // events whose float norms the scale corrects
 };
 // One of the row's phase events: its qubit and the shared runs it joins (INT32_MIN: none).
 struct TabEvent {

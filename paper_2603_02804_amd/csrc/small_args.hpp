@@ -36,7 +36,7 @@ struct EventArgs {
   const ThrBase* tbases;
   const TabEvent* tevs;
   const CzGroup* czg;
-  const PhaEntry* phas;
+  const int32_t* tcor;
   const double* dsh;
   float* tab;
   float* tco;
@@ -136,7 +136,7 @@ inline EventArgs make_event_args(const PlanCore& c, const PlanPtrs& d, const Coe
   a.tbases = d.tbases;
   a.tevs = d.tevs;
   a.czg = d.czg;
-  a.phas = d.phas;
+  a.tcor = d.tcor;
   a.dsh = cp.dsh;
   a.tab = cp.tab;
   a.tco = cp.tco;

@@ -196,16 +196,14 @@ __device__ inline float2 shared_event(const double* dsh, const EventRec& e) {
 }
 
 // The scale that a row of the epoch tables owes: of its shared runs' rotations, and of
-// the rounded norms of the phases that it applies to register-held qubits.
+// the rounded norms of the shared phases that the pass kernel applies itself.
 __device__ inline double row_scale(const EventArgs& a, const TabRec* r) {
   double scale = 1.0;
 #pragma unroll
   for (int j = 0; j < kMaxR; ++j)
     if (r->ref[j] != INT32_MIN) scale *= a.dsh[kDshRow * (long long)r->ref[j] + 4];
-  for (int i = 0; i < r->pha_count; ++i) {
-    const int ref = a.phas[r->pha_first + i].ref;
-    if (ref < 0) continue;
-    const float2 w = shared_event(a.dsh, a.T.events[ref]);
+  for (int i = 0; i < r->cor_count; ++i) {
+    const float2 w = shared_event(a.dsh, a.T.events[a.tcor[r->cor_first + i]]);
     scale /= sqrt((double)w.x * w.x + (double)w.y * w.y);
   }
   return scale;
