@@ -746,8 +746,8 @@ qf_status qf_plan_create(const qf_circuit* circuit, int32_t batch, const qf_tuni
   if (st == QF_OK && !p->core.per_gate && p->core.off_ext <= QF_NOALLOC_SCRATCH_BYTES &&
       p->core.off_ext + p->core.ext_bytes > QF_NOALLOC_SCRATCH_BYTES &&
       hipMalloc((void**)&p->noalloc_ext, p->core.ext_bytes) != hipSuccess) {
-    st = QF_ERR_OOM;
-    msg = "hipMalloc of epoch tables failed";
+    p->noalloc_ext = nullptr;  // every call but qf_forward_noalloc (then refused) works without
+    (void)hipGetLastError();
   }
   if (st != QF_OK) {
     qf_plan_destroy(p);
@@ -829,9 +829,10 @@ qf_status qf_plan_get_info(const qf_plan* p, qf_plan_info* info) {
   // fused 2x2 complex matrix per run): forward and recompute apply it (8
   // multiply-adds, 16 flops); the adjoint pass un-applies it from psi and
   // lambda and forms the gradient inner products (about 24 multiply-adds, 48
-  // flops).  The kernels execute fewer: the run is a real RY between diagonal
-  // phases, applied as three shears (6 flops per amplitude), so the adjoint pass
-  // executes 2 x 6 + 12 (three functionals) = 24 flops per amplitude and run.
+  // flops).  The kernels execute fewer: the run is a real RY between diagonal phases,
+  // applied without its cosine (4 flops per amplitude; 6 as shears with five register
+  // qubits), so the adjoint pass executes 2 x 4 + 12 (three functionals) = 20 flops per
+  // amplitude and run.
   const double runs = (double)S.n_u2;
   info->fwd_flops_per_sample = runs * 16 * A;
   double rec_runs = 0;
@@ -843,7 +844,7 @@ qf_status qf_plan_get_info(const qf_plan* p, qf_plan_info* info) {
   info->bwd_pass_flops_per_sample = runs * 48 * A;
   info->bwd_flops_per_sample = info->bwd_pass_flops_per_sample + rec_runs * 16 * A +
                                (c.store ? 0 : info->fwd_flops_per_sample);
-  info->exec_bwd_pass_flops_per_sample = runs * 24 * A;
+  info->exec_bwd_pass_flops_per_sample = runs * (S.R <= 4 ? 20 : 24) * A;
   info->bwd_pass_launches = (int64_t)c.P * ((c.B + c.mb - 1) / c.mb);
   return QF_OK;
 }
