@@ -1,6 +1,6 @@
 """The default end-of-pass threshold on circuits that the entanglers serialise: the
 planner keeps the cheapest of its schedules, and that schedule's programs (run by the
-CPU checker) agree with the oracle."""
+CPU execution of its programs) agree with the oracle."""
 import numpy as np
 import pytest
 
