@@ -151,6 +151,8 @@ struct PhaEntry {
 // its index alone and not on one another.
 // kEpochNoX: every run of the group is RY gates followed by RZ gates.  Their generators
 // have no X part at the cut after the run's RY, so the adjoint leaves that functional out.
+// That cut is the split's: it must put the run's whole RZ after its RY also where the RY
+// part vanishes and the split is not unique.
 enum EpochFlags : int32_t {
   kEpochPs = 1, kEpochLoop = 2, kEpochPhaseA = 4, kEpochCza = 8, kEpochStay = 16, kEpochNoX = 32
 };

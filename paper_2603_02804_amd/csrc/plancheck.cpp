@@ -143,8 +143,10 @@ struct CpuExec {
     const double nrm = std::sqrt(a0 * a0 + b0 * b0);
     o.cb = a0 / nrm;
     o.sb = b0 / nrm;
-    const cd A = a0 > 1e-300 ? V.m[0] / a0 : cd(1, 0);
-    const cd Bp = b0 > 1e-300 ? V.m[2] / b0 : cd(1, 0);
+    cd A = a0 > 1e-300 ? V.m[0] / a0 : cd(1, 0);
+    cd Bp = b0 > 1e-300 ? V.m[2] / b0 : cd(1, 0);
+    if (b0 <= 1e-300) Bp = std::conj(A);   // c = 0, as the device's split
+    if (a0 <= 1e-300) A = std::conj(Bp);
     o.z = A * std::conj(Bp);
     o.u = std::polar(1.0, 0.5 * std::arg(o.z));
     o.v = A * std::conj(o.u);
@@ -483,7 +485,7 @@ struct CpuExec {
                 if (fe.slot < 0 || fe.slot >= ns || pf + 3 > (int64_t)L.nb * tiles * 3 * ns) oob("partF");
                 float* dst = L.partF + pf;
                 in_ws(dst, 12, "partF address");
-                dst[0] = fw[0];
+                dst[0] = op.d ? 0.f : fw[0];   // (kEpochNoX: the pass kernels leave it out)
                 dst[1] = fw[1];
                 dst[2] = fw[2];
               }
@@ -521,7 +523,8 @@ struct CpuExec {
         for (int j = 0; j < 32; ++j) cnt += (e.ry_b >> j) & 1;
         ry.push_back({OP_RYG, cnt, e.ry_a, e.ry_b, 0, 0, 0, 0});
       }
-      if (e.func_count > 0) func.push_back({OP_FUNC, e.func_count, e.func_first, 0, 0, 0, 0, 0});
+      if (e.func_count > 0)
+        func.push_back({OP_FUNC, e.func_count, e.func_first, 0, e.flags & kEpochNoX, 0, 0, 0});
       auto add = [&](const std::vector<Op>& v) { out.insert(out.end(), v.begin(), v.end()); };
       if (!bwd) { add(perm); add(diag); add(pha); add(cza); add(ry); }
       else { add(func); add(ry); add(cza); add(pha); add(diag); add(perm); }
