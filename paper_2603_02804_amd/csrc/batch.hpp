@@ -473,7 +473,10 @@ inline bool check_program(const std::vector<CircProgram>& cps, const std::vector
         return false;
       }
     for (size_t i = 0; i < cp.sj.size(); ++i)
-      if (cp.sj[i].circ != (int)ci || !check_small_job(cp.sj[i], *cores[ci], regions[ci])) {
+      if (cp.sblocks[i] == 0) {
+        if (msg) *msg = "small job " + std::to_string(i) + " of circuit " + std::to_string(ci) + " has no workgroups";
+        return false;
+      } else if (cp.sj[i].circ != (int)ci || !check_small_job(cp.sj[i], *cores[ci], regions[ci])) {
         if (msg) *msg = "small job " + std::to_string(i) + " of circuit " + std::to_string(ci) +
                         " reaches outside its workspace region";
         return false;

@@ -181,9 +181,10 @@ inline ReduceEArgsT<Real> make_reduce_E_args(const PlanCore& c, int nb, int samp
   a.wide = parts > 16 ? 1 : 0;
   return a;
 }
+// (a circuit without observables: one idle workgroup, an empty grid is a launch error)
 template <class Real>
 inline long long reduce_E_blocks(const ReduceEArgsT<Real>& a) {
-  return a.wide ? a.nb : ((long long)a.nb * a.K + kSmallThreads - 1) / kSmallThreads;
+  return a.wide ? a.nb : (long long)blocks_for((long long)a.nb * a.K);
 }
 
 inline FsumArgs make_fsum_args(const PlanCore& c, const PlanPtrs& d, int seg, int nb, const float* partF,
