@@ -141,9 +141,7 @@ __device__ __forceinline__ void apply_rot(float2 (&a)[1 << R], float t) {
 }
 
 // The rotations of all register bits, bits 0..R-1 in order, straight-line code.  Four
-// bits or fewer: unscaled (t = tan f), which may grow a state by 2^100 until the
-// factor is applied; five: as shears (t = tan(f/2), s = sin f), since a fifth unscaled
-// rotation could overflow.
+// bits or fewer: unscaled (t = tan f); five: as shears (t = tan(f/2), s = sin f).
 template <int R>
 constexpr bool kScaledRot = R <= 4;
 template <int R, int J = 0>
@@ -523,22 +521,32 @@ struct PassCtx {
 
   // An epoch's run group: its coefficients stand in the epoch table, and the scale of
   // its shared runs in the table's pending factor; per-sample runs bring their own.
-  // tt, sn: the table row's coefficients.
+  // left: the product of the shared runs' cosines.  Runs, shared or per-sample, that
+  // would grow the state too far turn twice by half their angles (kMaxGrowth).
   __device__ __forceinline__ void epoch_group(float2 (&a)[NA], float2 (&l)[NA], float2& ph, const EpochRec* E,
-                                              int flags, float (&tt)[R], float (&sn)[R]) const {
+                                              int flags, float left, float (&tt)[R], float (&sn)[R]) const {
+    // (positive floats compare as integers)
+    const int least = __float_as_int(1.f / kMaxGrowth);
+    const bool twice = kScaledRot<R> && __float_as_int(left) < least;
+    bool ps_twice = false;
     if (flags & kEpochPs) {
       const int ps_mask = cld(&E->ps_mask);
-      double nrm = 1.0;
+      auto coefs = [&](int at) {   // tan f (at 6) or tan(f/2) (at 7)
+        double nrm = 1.0;
 #pragma unroll
-      for (int j = 0; j < R; ++j)
-        if ((ps_mask >> j) & 1) {
-          const float* cp = run_coef(A, cld(&E->ref[j]), sample);
-          tt[j] = cld(cp + 6);
-          sn[j] = cld(cp + 1);
-          nrm *= fma((double)tt[j], (double)tt[j], 1.0);
-        }
+        for (int j = 0; j < R; ++j)
+          if ((ps_mask >> j) & 1) {
+            const float* cp = run_coef(A, cld(&E->ref[j]), sample);
+            tt[j] = cld(cp + at);
+            sn[j] = cld(cp + 1);
+            nrm *= fma((double)tt[j], (double)tt[j], 1.0);
+          }
+        return nrm;
+      };
+      float sc = (float)rsqrt(coefs(6));
       if constexpr (kScaledRot<R>) {
-        const float sc = (float)rsqrt(nrm);
+        ps_twice = __builtin_amdgcn_readfirstlane(__float_as_int(sc)) < least;
+        if (ps_twice) sc = (float)(1.0 / coefs(7));
         ph.x *= sc;
         ph.y *= sc;
       }
@@ -552,6 +560,15 @@ struct PassCtx {
     }
     apply_group<R>(a, tt, sn);
     if constexpr (BWD) apply_group<R>(l, tt, sn);
+    // (a loop around both made the reads of LDS ahead of it wait: 5%)
+    if (__builtin_expect(twice || ps_twice, 0)) {
+      const int ps_mask = flags & kEpochPs ? cld(&E->ps_mask) : 0;
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        if (!((ps_mask >> j) & 1 ? ps_twice : twice)) tt[j] = 0.f;
+      apply_group<R>(a, tt, sn);
+      if constexpr (BWD) apply_group<R>(l, tt, sn);
+    }
   }
 
   // The tile from memory into `layout`.  Every lane loads: the thread tables are zero above
@@ -572,6 +589,19 @@ struct PassCtx {
     }
   }
 
+  // lambda is at most 2 sum_k |dE_k| times psi: large upstream gradients leave no room for
+  // kMaxGrowth below the end of the float range.  There lambda is kept 2^32 times smaller,
+  // and the functionals get it back.
+  __device__ __forceinline__ float lambda_scale() const {
+    const int* g = reinterpret_cast<const int*>(A.dE + (size_t)sample * A.K);
+    int most = 0;
+    for (int k0 = 0; k0 < A.K; k0 += 8) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) most = max(most, cld(g + min(k0 + k, A.K - 1)) & 0x7fffffff);
+    }
+    return most > __float_as_int(0x1p32f) ? 0x1p-32f : 1.f;
+  }
+
   // Adjoint seed of general Pauli strings, lambda = 2 sum_k g_k P_k psi (App. B.2), from the
   // stored output state that the pass loads as psi; masks in its bit order, which is also
   // the load's.  (P psi)_y = i^ny (-1)^{popcount((y ^ xm) & zm)} psi_{y ^ xm}.  A kernel of
@@ -582,13 +612,14 @@ struct PassCtx {
     rb.load((A.layouts + layout)->mem_reg);
     const float2* src = reinterpret_cast<const float2*>(A.src0) + sl * A.s0;
     const float* g = A.dE + (size_t)sample * A.K;
+    const float gs = lambda_scale();
 #pragma unroll
     for (int jj = 0; jj < NA; ++jj) l[jj] = make_float2(0.f, 0.f);
 #pragma unroll 1
     for (int k = 0; k < A.K; ++k) {
       const uint32_t xm = cld(&A.pauli[k].xm), zm = cld(&A.pauli[k].zm);
       const int ny = cld(&A.pauli[k].ny);
-      const float gk = cld(g + k);
+      const float gk = gs * cld(g + k);
       // g i^ny
       const float gr = (ny & 1) ? 0.f : (ny & 2) ? -gk : gk, gi = (ny & 1) ? ((ny & 2) ? -gk : gk) : 0.f;
       float2 v[NA];
@@ -844,12 +875,13 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
       RegBits<R> rb;
       rb.load((A.layouts + op.a)->log_reg);
       const float* g = A.dE + (size_t)sample * A.K;
+      const float gs = cx.lambda_scale();
       float c[NA];
 #pragma unroll
       for (int jj = 0; jj < NA; ++jj) c[jj] = 0.f;
 #pragma unroll 1
       for (int k = 0; k < A.K; ++k) {
-        const float gk = cld(g + k);
+        const float gk = gs * cld(g + k);
         const uint32_t zk = cld(A.zmask + k);
 #pragma unroll
         for (int jj = 0; jj < NA; ++jj) c[jj] += (__popc((base | rb(jj)) & zk) & 1) ? -gk : gk;
@@ -921,8 +953,9 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
 #pragma unroll
       for (int j = 0; j < R; ++j) {
         tt[j] = cld(row + j);
-        sn[j] = kScaledRot<R> ? 0.f : cld(row + 8 + j);
+        sn[j] = kScaledRot<R> ? 0.f : cld(row + kTabSine + j);
       }
+      const float left = kScaledRot<R> ? cld(row + kTabLeft) : 1.f;
       // nb: the thread's bases after the exchange; owed: what it owes when this epoch's
       // exchange sends its amplitudes, one table entry in place of the epoch's
       // diagonal items and scale factors
@@ -949,11 +982,11 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
               cx.phasea(a, l, cld(&A.phas[p].regbit), cld(&A.phas[p].ref));
           if (flags & kEpochCza) cx.cza(a, l, ph, cld(&E->cza), cx.tlog | cur.y);
         }
-        cx.epoch_group(a, l, ph, E, flags, tt, sn);
+        cx.epoch_group(a, l, ph, E, flags, left, tt, sn);
       } else {
         // the tile is in the layout before the PERM that ends the epoch
         cx.func(a, l, sl, (flags & kEpochNoX) != 0);
-        cx.epoch_group(a, l, ph, E, flags, tt, sn);
+        cx.epoch_group(a, l, ph, E, flags, left, tt, sn);
         if (flags & (kEpochLoop | kEpochPhaseA | kEpochCza)) {
           if (flags & kEpochCza) cx.cza(a, l, ph, cld(&E->cza), cx.tlog | cur.y);
           if (flags & kEpochPhaseA)
@@ -1009,13 +1042,14 @@ __device__ __forceinline__ void pass_body(const KArgs& A, const int item) {
   if constexpr (BWD) {
     // one partial sum per tile and functional: add the waves' sums
     if (n_slots > 0) {
+      const float unscale = 1.f / cx.lambda_scale();
       __syncthreads();
       const float* part = qf_pass_part;
       for (int i = wave * 64 + (int)cx.lane_id(); i < 3 * n_slots; i += NT) {
         float acc = 0.f;
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) acc += part[w * 3 * n_slots + i];
-        A.partF[(size_t)item * 3 * n_slots + i] = acc;
+        A.partF[(size_t)item * 3 * n_slots + i] = unscale * acc;
       }
     }
   }

@@ -126,14 +126,14 @@ __device__ inline D2 run_matrix(const Tabs& T, const RunRec& rr, const Real* the
   return U;
 }
 
-// Least cosine of a scaled rotation: t = tan f stays below 2^25, so that four unscaled
-// rotations grow a state by less than 2^100.  The cosine moves by less than half an
-// ulp of 1, the rounding of the rotated amplitudes.
+// Least cosine of a scaled rotation: t = tan f stays below 2^25 and the growth of four
+// below 2^100.  The cosine moves by less than half an ulp of 1, the rounding of the
+// rotated amplitudes.
 constexpr double kMinCos = 1.0 / (1 << 25);
 
 // Run coefficients, f = b/2 of the RZ(a) RY(b) RZ(c) split.
 //   kFormShear   [cos f, sin f, u, v, tan(f/2), 0]
-//   kFormScaled  [cos f, sin f, u, v, t = tan f, 0]
+//   kFormScaled  [cos f, sin f, u, v, t = tan f, tan(f/2)]
 //   kFormMatrix  the 2x2 matrix row-major (one-gate runs of the per-gate paths)
 // Shared runs of the split forms also leave as doubles (dsh) u, v and the scale that
 // an unscaled rotation owes: 1/sqrt(1 + t^2) of the float t, so that no norm is lost.
@@ -158,8 +158,9 @@ __device__ inline void coef_body(const CoefArgsT<Real>& a, long long idx) {
     const ZYZ z = zyz_split(U);
     // f in [0, pi/2]
     double scale = 1.0;
-    Real t;
+    Real t, half = 0;
     if (a.form == kFormScaled) {
+      half = (Real)(z.sb / (1.0 + z.cb));
       t = (Real)(z.sb / fmax(z.cb, kMinCos));
       scale = 1.0 / sqrt(1.0 + (double)t * (double)t);
     } else {
@@ -169,7 +170,7 @@ __device__ inline void coef_body(const CoefArgsT<Real>& a, long long idx) {
     out[2] = (Real)z.ur; out[3] = (Real)z.ui;
     out[4] = (Real)z.vr; out[5] = (Real)z.vi;
     out[6] = t;
-    out[7] = 0;
+    out[7] = half;
     if (idx < a.n_sh) {
       double* d = a.dsh + kDshRow * idx;
       d[0] = z.ur; d[1] = z.ui;
@@ -200,13 +201,31 @@ __device__ inline float2 shared_event(const double* dsh, const EventRec& e) {
   return make_float2((float)wr, (float)wi);
 }
 
+// The scale that a row's shared runs owe as rotations by f, and whether they turn twice
+// (rounded as the pass kernel compares it).
+__device__ inline double row_left(const EventArgs& a, const TabRec* r, bool* twice) {
+  double left = 1.0;
+#pragma unroll
+  for (int j = 0; j < kMaxR; ++j)
+    if (r->ref[j] != INT32_MIN) left *= a.dsh[kDshRow * (long long)r->ref[j] + 4];
+  *twice = (float)left < 1.f / kMaxGrowth;
+  return left;
+}
+
 // The scale that a row of the epoch tables owes: of its shared runs' rotations, and of
 // the rounded norms of the shared phases that the pass kernel applies itself.
 __device__ inline double row_scale(const EventArgs& a, const TabRec* r) {
-  double scale = 1.0;
-#pragma unroll
-  for (int j = 0; j < kMaxR; ++j)
-    if (r->ref[j] != INT32_MIN) scale *= a.dsh[kDshRow * (long long)r->ref[j] + 4];
+  bool twice;
+  double scale = row_left(a, r, &twice);
+  if (twice) {   // 1/(1 + h^2) of h = tan(f/2) each
+    double halves = 1.0;
+    for (int j = 0; j < kMaxR; ++j)
+      if (r->ref[j] != INT32_MIN) {
+        const double h = a.csh[8 * (long long)r->ref[j] + 7];
+        halves *= 1.0 + h * h;
+      }
+    scale = 1.0 / halves;
+  }
   for (int i = 0; i < r->cor_count; ++i) {
     const float2 w = shared_event(a.dsh, a.T.events[a.tcor[r->cor_first + i]]);
     scale /= sqrt((double)w.x * w.x + (double)w.y * w.y);
@@ -278,7 +297,11 @@ __device__ inline void table_body(const EventArgs& a, int blk, int thread, doubl
   if (t < kTabCoefs) {
     const int j = t & 7;
     const bool present = j < kMaxR && r->ref[j] != INT32_MIN;
-    a.tco[(long long)row * kTabCoefs + t] = present ? a.csh[8 * (long long)r->ref[j] + (t < 8 ? 6 : 1)] : 0.f;
+    bool twice;
+    const double left = row_left(a, r, &twice);
+    float v = present ? a.csh[8 * (long long)r->ref[j] + (t >= kTabSine ? 1 : twice ? 7 : 6)] : 0.f;
+    if (t == kTabLeft && a.form == kFormScaled) v = (float)left;
+    a.tco[(long long)row * kTabCoefs + t] = v;
   }
 }
 
