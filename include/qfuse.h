@@ -230,9 +230,13 @@ qf_status qf_forward(qf_plan* plan, const float* theta, const float* x, float* E
  * array and leaves its contents there, so calls that overlap on one GPU (several
  * streams or host threads) race and must be ordered by the caller; no
  * qf_backward can follow this call (its checkpoints live in the shared array).
- * Errors: those of qf_forward, QF_ERR_WORKSPACE when qf_workspace_size of the
- * plan exceeds QF_NOALLOC_SCRATCH_BYTES (use qf_forward), QF_ERR_DEVICE when the
- * array's device address cannot be obtained.
+ * Errors: those of qf_forward, QF_ERR_WORKSPACE when the plan's workspace exceeds
+ * QF_NOALLOC_SCRATCH_BYTES (use qf_forward), QF_ERR_DEVICE when the array's device
+ * address cannot be obtained.  Not counted are the tables that the calls form of
+ * their angles and the sums of the gradients, at the end of the workspace: a plan
+ * with a qf_workspace_size somewhat above the limit is accepted.  Tables that fit
+ * nowhere in the array (very deep circuits close to the limit) get memory of their
+ * own when the plan is created; the call is refused if there was none left.
  */
 #define QF_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 qf_status qf_forward_noalloc(qf_plan* plan, const float* theta, const float* x, float* E, void* stream);

@@ -325,7 +325,7 @@ qf_status qf_batch_create(const qf_circuit* const* circuits, const int32_t* samp
   for (int i = 0; i < n_circuits; ++i) {
     qf_plan* p = nullptr;
     const qf_tuning ct = batch_plan_tuning(bt, circuits[i]->c.n);
-    const qf_status st = qf_plan_create(circuits[i], samples[i], &ct, &p);
+    const qf_status st = create_plan(circuits[i], samples[i], &ct, false, &p);
     if (st != QF_OK) {
       const std::string m = "circuit " + std::to_string(i) + ": " + qf_last_error();
       destroy_batch(b);

@@ -258,6 +258,16 @@ inline qf_status build_plan_core(const Circuit& C, int B, const Tuning& T, PlanC
   return QF_OK;
 }
 
+// Where a forward that no backward follows keeps the epoch tables in a workspace of `limit`
+// bytes: in their own place, or over what only a backward uses (adjoint states and stored
+// pass outputs, functionals and gradient rows).  -1: nowhere.
+inline int64_t forward_tables(const PlanCore& c, size_t limit) {
+  if (c.off_ext + c.ext_bytes <= limit) return (int64_t)c.off_ext;
+  if (c.off_partF + c.ext_bytes <= limit) return (int64_t)c.off_partF;
+  if (c.off_seg + c.ext_bytes <= c.off_partE && c.off_partF <= limit) return (int64_t)c.off_seg;
+  return -1;
+}
+
 // The observables as Pauli records in the bit order of the state they are
 // applied to: logical for the per-gate paths, the last pass's output order for
 // the fused path.

@@ -177,6 +177,8 @@ struct Profiler {
 // Records the message of the failing C-ABI call and returns its status.
 qf_status set_error(qf_status s, const std::string& m);
 
+// qf_plan_create; noalloc: the plan may be given to qf_forward_noalloc.
+qf_status create_plan(const qf_circuit* circuit, int32_t batch, const qf_tuning* tuning, bool noalloc, qf_plan** out);
 // True when a pass kernel is compiled for the tile shape.
 bool have_pass_kernel(int R, int NT);
 
@@ -190,7 +192,7 @@ struct qf_plan {
   qf::PlanCore core;
   qf::DevPlan dev;
   // epoch tables of qf_forward_noalloc, only where the library's array holds the rest of
-  // the plan's workspace but not them
+  // the plan's workspace and has no room left for them
   char* noalloc_ext = nullptr;
   int device = 0;
   qf::Profiler prof;

@@ -823,10 +823,11 @@ int qfc_stats(const qf_circuit_desc* desc, int32_t batch, const qf_tuning* tunin
   PlanCore pc;
   st = build_plan_core(C, batch, T, &pc, &msg);
   if (st != QF_OK) { g_err = msg; return st; }
-  int64_t v[17] = {pc.P, pc.n_seg, pc.ckpt, pc.mb, pc.S.n_perm, pc.S.n_u2, pc.S.n_cz, (int64_t)pc.S.layouts.size(),
+  int64_t v[20] = {pc.P, pc.n_seg, pc.ckpt, pc.mb, pc.S.n_perm, pc.S.n_u2, pc.S.n_cz, (int64_t)pc.S.layouts.size(),
                    (int64_t)pc.S.runs.size(), pc.S.k, pc.S.R, (int64_t)pc.ws_bytes, pc.S.n_diag_thread,
-                   pc.S.n_diag_amp, pc.S.NT, pc.S.thread_bits, pc.per_gate ? 1 : lds_bank_degree(pc.S)};
-  for (int i = 0; i < n_out && i < 17; ++i) out[i] = v[i];
+                   pc.S.n_diag_amp, pc.S.NT, pc.S.thread_bits, pc.per_gate ? 1 : lds_bank_degree(pc.S),
+                   (int64_t)pc.off_ext, (int64_t)pc.ext_bytes, forward_tables(pc, size_t(64) << 20)};
+  for (int i = 0; i < n_out && i < 20; ++i) out[i] = v[i];
   return 0;
 }
 

@@ -675,6 +675,13 @@ qf_status qf_circuit_destroy(qf_circuit* c) {
 }
 
 qf_status qf_plan_create(const qf_circuit* circuit, int32_t batch, const qf_tuning* tuning, qf_plan** out) {
+  return create_plan(circuit, batch, tuning, true, out);
+}
+
+}  // extern "C"
+
+qf_status qf::create_plan(const qf_circuit* circuit, int32_t batch, const qf_tuning* tuning, bool noalloc,
+                          qf_plan** out) {
   if (!out) return fail(QF_ERR_INVALID_ARG, "out is NULL");
   *out = nullptr;
   if (!circuit) return fail(QF_ERR_INVALID_ARG, "circuit is NULL");
@@ -743,8 +750,9 @@ qf_status qf_plan_create(const qf_circuit* circuit, int32_t batch, const qf_tuni
     hipGetDevice(&p->device);
     st = upload_plan(p->core, &p->dev, &msg);
   }
-  if (st == QF_OK && !p->core.per_gate && p->core.off_ext <= QF_NOALLOC_SCRATCH_BYTES &&
-      p->core.off_ext + p->core.ext_bytes > QF_NOALLOC_SCRATCH_BYTES &&
+  // tables that fit nowhere beside the rest of a forward's workspace are the plan's own
+  if (st == QF_OK && noalloc && !p->core.per_gate && p->core.off_ext <= QF_NOALLOC_SCRATCH_BYTES &&
+      forward_tables(p->core, QF_NOALLOC_SCRATCH_BYTES) < 0 &&
       hipMalloc((void**)&p->noalloc_ext, p->core.ext_bytes) != hipSuccess) {
     p->noalloc_ext = nullptr;  // every call but qf_forward_noalloc (then refused) works without
     (void)hipGetLastError();
@@ -756,6 +764,8 @@ qf_status qf_plan_create(const qf_circuit* circuit, int32_t batch, const qf_tuni
   *out = p;
   return QF_OK;
 }
+
+extern "C" {
 
 qf_status qf_plan_destroy(qf_plan* p) {
   if (!p) return QF_OK;
@@ -849,7 +859,7 @@ qf_status qf_plan_get_info(const qf_plan* p, qf_plan_info* info) {
   return QF_OK;
 }
 
-// need: the workspace the call uses (default: the plan's)
+// need: the least workspace the call takes (default: the plan's)
 static qf_status check_call(qf_plan* p, void* ws, size_t ws_bytes, size_t need = 0) {
   if (!p) return fail(QF_ERR_INVALID_ARG, "plan is NULL");
   if (!need) need = p->core.ws_bytes;
@@ -884,24 +894,27 @@ qf_status qf_forward(qf_plan* p, const float* theta, const float* x, float* E, v
 
 qf_status qf_forward_noalloc(qf_plan* p, const float* theta, const float* x, float* E, void* stream) {
   if (!p) return fail(QF_ERR_INVALID_ARG, "plan is NULL");
-  // the epoch tables that do not fit behind the rest are the plan's own
   const PlanCore& c = p->core;
-  const size_t need = c.per_gate ? c.ws_bytes : c.off_ext + (p->noalloc_ext ? 0 : c.ext_bytes);
-  if (need > QF_NOALLOC_SCRATCH_BYTES)
-    return fail(QF_ERR_WORKSPACE, "qf_forward_noalloc: the plan needs a workspace of " +
-                                      std::to_string(p->core.ws_bytes) + " bytes, more than the " +
-                                      std::to_string((size_t)QF_NOALLOC_SCRATCH_BYTES) +
+  const size_t limit = QF_NOALLOC_SCRATCH_BYTES, need = c.per_gate ? c.ws_bytes : c.off_ext;
+  if (need > limit)
+    return fail(QF_ERR_WORKSPACE, "qf_forward_noalloc: the plan needs a workspace of " + std::to_string(need) +
+                                      " bytes (without its epoch tables), more than the " + std::to_string(limit) +
                                       "-byte library array; use qf_forward with a caller workspace");
+  const int64_t tables = c.per_gate || p->noalloc_ext ? 0 : forward_tables(c, limit);
+  if (tables < 0)
+    return fail(QF_ERR_WORKSPACE, "qf_forward_noalloc: no memory was left at the plan's creation for its " +
+                                      std::to_string(c.ext_bytes) + " bytes of epoch tables, which do not fit the " +
+                                      std::to_string(limit) + "-byte library array beside the rest");
   void* ws = nullptr;
   std::string msg;
   if (!noalloc_scratch(&ws, &msg)) return fail(QF_ERR_DEVICE, msg);
-  qf_status st = check_call(p, ws, QF_NOALLOC_SCRATCH_BYTES, need);
+  qf_status st = check_call(p, ws, limit, need);
   if (st != QF_OK) return st;
   if (c.c128) return fail(QF_ERR_INVALID_ARG, "complex128 plan: call qf_forward_c128");
   if (!E || (c.C.P > 0 && !theta) || (c.C.F > 0 && !x)) return fail(QF_ERR_INVALID_ARG, "NULL buffer");
   // no profiling events on this path: it creates nothing
   GpuExec ex(c, p->dev, (hipStream_t)stream);
-  ex.ext = p->noalloc_ext;
+  ex.ext = p->noalloc_ext ? p->noalloc_ext : (char*)ws + tables;
   ex.forward_only = true;
   st = run_forward(c, ex, theta, x, E, (char*)ws, nullptr);
   if (st != QF_OK) return fail(st, ex.msg);
