@@ -1048,7 +1048,7 @@ bool build_schedule(const Circuit& C, const Tuning& T, Schedule* Sp, std::string
     Tuning t = T;
     t.fill = fill;
     Schedule alt;
-    if (!build_with_fill(C, t, &alt, msg)) return false;
+    if (!build_with_fill(C, t, &alt, nullptr)) continue;   // (the schedule in hand stands)
     // (512 functional slots of a pass fit the LDS of any tile shape)
     if (schedule_cost(alt) < schedule_cost(*Sp) && alt.max_slots <= std::max(512, Sp->max_slots)) *Sp = std::move(alt);
   }
