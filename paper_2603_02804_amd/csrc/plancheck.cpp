@@ -129,8 +129,7 @@ struct CpuExec {
     }
   }
 
-  const float* ev_sh = nullptr;
-  const float* ev_ps = nullptr;
+  CoefPtrs cp;   // coefficients, phase events, epoch tables and generators in the workspace
 
   // RZ(a) RY(b) RZ(c) split: (cos b/2, sin b/2, e^{-ia/2}, e^{-ic/2}) and e^{-ia}.
   struct Split {
@@ -156,50 +155,123 @@ struct CpuExec {
   void coef(const float* th, const float* xx, char* ws) {
     theta = th;
     x = xx;
-    float* csh = at<float>(ws, c.off_coef_sh);
-    float* cps = at<float>(ws, c.off_coef_ps);
-    float* esh = at<float>(ws, c.off_ev_sh);
-    float* eps = at<float>(ws, c.off_ev_ps);
+    cp = coef_ptrs(c, ws);
+    const Schedule& S = c.S;
+    float* csh = const_cast<float*>(cp.csh);
+    float* cps = const_cast<float*>(cp.cps);
     coef_sh = csh;
     coef_ps = cps;
-    ev_sh = esh;
-    ev_ps = eps;
-    auto put_run = [&](float* dst, int r, int b) {
+    const bool scaled = run_form(S.R) == kFormScaled;
+    auto put_run = [&](float* dst, int r, int b, double* d) {
       const M2 U = run_matrix(r, b);
       if (c.per_gate) {
         put(dst, U);
         return;
       }
       const Split z = split(U);
+      const float half = (float)(z.sb / (1.0 + z.cb));
+      const float t = scaled ? (float)(z.sb / std::max(z.cb, kMinCos)) : half;
       const float v[8] = {(float)z.cb, (float)z.sb, (float)z.u.real(), (float)z.u.imag(),
-                          (float)z.v.real(), (float)z.v.imag(), (float)(z.sb / (1.0 + z.cb)), 0.f};
+                          (float)z.v.real(), (float)z.v.imag(), t, scaled ? half : 0.f};
       std::memcpy(dst, v, sizeof(v));
+      if (!d) return;
+      const double w[5] = {z.u.real(), z.u.imag(), z.v.real(), z.v.imag(),
+                           scaled ? 1.0 / std::sqrt(1.0 + (double)t * t) : 1.0};
+      std::memcpy(d, w, sizeof(w));
     };
-    for (size_t i = 0; i < c.coef_runs_sh.size(); ++i) put_run(csh + 8 * i, c.coef_runs_sh[i], 0);
+    for (size_t i = 0; i < c.coef_runs_sh.size(); ++i)
+      put_run(csh + 8 * i, c.coef_runs_sh[i], 0, c.per_gate ? nullptr : cp.dsh + kDshRow * i);
     const int nps = (int)c.coef_runs_ps.size();
     for (int b = 0; b < c.B; ++b)
-      for (int i = 0; i < nps; ++i) put_run(cps + 8 * ((int64_t)b * nps + i), c.coef_runs_ps[i], b);
-    auto ev = [&](const EventRec& e, int b, float* out) {
-      cf w(1.f, 0.f);
-      if (e.prev_ref != INT32_MIN) {
-        const float* p = coef_row(e.prev_ref, b);
-        w = w * cf(p[2], p[3]);
-      }
-      if (e.next_ref != INT32_MIN) {
-        const float* p = coef_row(e.next_ref, b);
-        w = w * cf(p[4], p[5]);
-      }
+      for (int i = 0; i < nps; ++i) put_run(cps + 8 * ((int64_t)b * nps + i), c.coef_runs_ps[i], b, nullptr);
+    if (c.per_gate) return;
+    auto put_c = [](float* out, cf w) {
       out[0] = w.real();
       out[1] = w.imag();
     };
-    for (int i = 0; i < c.S.n_ev_shared; ++i) ev(c.S.events[i], 0, esh + 2 * i);
+    for (int i = 0; i < S.n_ev_shared; ++i) put_c(const_cast<float*>(cp.esh) + 2 * i, cf(shared_event(S.events[i])));
     for (int b = 0; b < c.B; ++b)
-      for (int i = 0; i < c.S.n_ev_ps; ++i)
-        ev(c.S.events[c.S.n_ev_shared + i], b, eps + 2 * ((int64_t)b * c.S.n_ev_ps + i));
+      for (int i = 0; i < S.n_ev_ps; ++i) {
+        const EventRec& e = S.events[S.n_ev_shared + i];
+        cf w(1.f, 0.f);
+        if (e.prev_ref != INT32_MIN) w *= cf(coef_row(e.prev_ref, b)[2], coef_row(e.prev_ref, b)[3]);
+        if (e.next_ref != INT32_MIN) w *= cf(coef_row(e.next_ref, b)[4], coef_row(e.next_ref, b)[5]);
+        put_c(const_cast<float*>(cp.eps) + 2 * ((int64_t)b * S.n_ev_ps + i), w);
+      }
+    tables();
+    for (int r : c.coef_runs_sh)
+      generators(r, 0, true, [&](int g, double nx, double ny, double nz) {
+        const double v[3] = {nx, ny, nz};
+        std::memcpy(cp.gvec + 3ll * g, v, sizeof(v));
+      });
+  }
+
+  // u(prev run) * v(next run) of shared runs, from the double rows
+  cd shared_event(const EventRec& e) const {
+    cd w(1, 0);
+    if (e.prev_ref != INT32_MIN) w *= cd(cp.dsh[kDshRow * e.prev_ref], cp.dsh[kDshRow * e.prev_ref + 1]);
+    if (e.next_ref != INT32_MIN) w *= cd(cp.dsh[kDshRow * e.next_ref + 2], cp.dsh[kDshRow * e.next_ref + 3]);
+    return w;
+  }
+
+  // The epoch tables (table_body of the device library).
+  double row_left(const TabRec& r) const {
+    double left = 1.0;
+    for (int j = 0; j < kMaxR; ++j)
+      if (r.ref[j] != INT32_MIN) left *= cp.dsh[kDshRow * r.ref[j] + 4];
+    return left;
+  }
+  static bool turns_twice(double left) { return (float)left < 1.f / kMaxGrowth; }
+  double row_scale(const TabRec& r) const {
+    double scale = row_left(r);
+    if (turns_twice(scale)) {
+      scale = 1.0;
+      for (int j = 0; j < kMaxR; ++j)
+        if (r.ref[j] != INT32_MIN) scale /= 1.0 + (double)coef_sh[8 * r.ref[j] + 7] * coef_sh[8 * r.ref[j] + 7];
+    }
+    for (int i = 0; i < r.cor_count; ++i) scale /= std::abs(cd(cf(shared_event(c.S.events[c.S.tcor[r.cor_first + i]]))));
+    return scale;
+  }
+  void tables() const {
+    const Schedule& S = c.S;
+    double carry = 1.0;
+    for (size_t row = 0; row < S.tabs.size(); ++row) {
+      const TabRec& r = S.tabs[row];
+      if (row % kCarryRows == 0) carry = 1.0;
+      const double owed = carry * row_scale(r), scale = (double)(float)owed;
+      carry = owed / scale;
+      for (int t = 0; t < S.active; ++t) {
+        uint32_t xl = 0, par = 0;
+        for (int i = 0; i < S.thread_bits; ++i)
+          if ((t >> i) & 1) xl ^= S.layouts[r.layout].log_thr[i];
+        for (int i = 0; i < r.czg_count; ++i) {
+          const CzGroup& g = S.czg[r.czg_first + i];
+          par ^= xl & (xl >> g.shift) & g.mask;
+        }
+        cd w(__builtin_popcount(par) & 1 ? -1 : 1, 0);
+        for (int i = 0; i < r.tev_count; ++i) {
+          const TabEvent& e = S.tevs[r.tev_first + i];
+          const cd f = shared_event({e.prev_ref, e.next_ref, 0, 0});
+          w *= (xl >> e.q) & 1 ? std::conj(f) : f;
+        }
+        float* out = cp.tab + 2 * (row * S.NT + t);
+        out[0] = (float)(scale * w.real());
+        out[1] = (float)(scale * w.imag());
+      }
+      float* co = cp.tco + row * kTabCoefs;
+      std::memset(co, 0, sizeof(float) * kTabCoefs);
+      const double left = row_left(r);
+      for (int j = 0; j < kMaxR; ++j)
+        if (r.ref[j] != INT32_MIN) {
+          co[j] = coef_sh[8 * r.ref[j] + (turns_twice(left) ? 7 : 6)];
+          co[kTabSine + j] = coef_sh[8 * r.ref[j] + 1];
+        }
+      if (run_form(S.R) == kFormScaled) co[kTabLeft] = (float)left;
+    }
   }
 
   cf event_w(int ref, int sample) const {
-    const float* p = ref >= 0 ? ev_sh + 2 * ref : ev_ps + 2 * ((int64_t)sample * c.S.n_ev_ps + (-1 - ref));
+    const float* p = ref >= 0 ? cp.esh + 2 * ref : cp.eps + 2 * ((int64_t)sample * c.S.n_ev_ps + (-1 - ref));
     return cf(p[0], p[1]);
   }
 
@@ -251,9 +323,205 @@ struct CpuExec {
           return v;
         };
         const int64_t item = (int64_t)sl * tiles + tile;
+        auto each = [&](auto f) {   // psi, and in the adjoint lambda
+          f(a);
+          if (L.bwd) f(l);
+        };
+        auto rotate = [&](std::vector<CF>& v, int j, float tt, float ss) {
+          for (int t = 0; t < active; ++t)
+            for (int jj = 0; jj < NA; ++jj) {
+              if ((jj >> j) & 1) continue;
+              CF &x0 = v[t * NA + jj], &x1 = v[t * NA + (jj | (1 << j))];
+              auto add = [](CF& y, float w, const CF& z) {
+                y.re = std::fma(w, z.re, y.re);
+                y.im = std::fma(w, z.im, y.im);
+              };
+              if (run_form(R) == kFormScaled) {
+                const CF y = x0;
+                add(x0, -tt, x1);
+                add(x1, tt, y);
+              } else {
+                add(x0, -tt, x1);
+                add(x1, ss, x0);
+                add(x0, -tt, x1);
+              }
+            }
+        };
+        // diagonal gates on thread-held qubits, into the pending factor
+        auto diagt = [&](int layout, int cz0, int n_cz, int ev0, int n_ev) {
+          const LayoutRec& Ly = S.layouts[layout];
+          for (int t = 0; t < active; ++t) {
+            const uint32_t xl = tlog | tbase(Ly.log_thr, t);
+            uint32_t par = 0;
+            for (int gi = 0; gi < n_cz; ++gi) {
+              const CzGroup& g = S.czg[cz0 + gi];
+              par ^= xl & (xl >> g.shift) & g.mask;
+            }
+            if (__builtin_popcount(par) & 1) ph[t] = -ph[t];
+            for (int ei = 0; ei < n_ev; ++ei) {
+              const PhaseEv& e = S.pev[ev0 + ei];
+              const cf w = event_w(e.ref, sample);
+              ph[t] *= (((xl >> e.q) & 1) != 0) != L.bwd ? std::conj(w) : w;
+            }
+          }
+        };
+        auto cza = [&](int rec, int layout) {
+          const CzaRec& cr = S.cza[rec];
+          const LayoutRec& Ly = S.layouts[layout];
+          for (int t = 0; t < active; ++t) {
+            const uint32_t xl = tlog | tbase(Ly.log_thr, t);
+            for (int jj = 0; jj < NA; ++jj) {
+              int sgn = (cr.sr >> jj) & 1;
+              for (int j = 0; j < R; ++j)
+                if ((jj >> j) & 1) sgn ^= __builtin_popcount(xl & cr.cmask[j]) & 1;
+              if (sgn) each([&](std::vector<CF>& v) { v[t * NA + jj] = CF{-v[t * NA + jj].re, -v[t * NA + jj].im}; });
+            }
+          }
+        };
+        auto phasea = [&](int bit, int ref) {
+          cf w = event_w(ref, sample);
+          if (L.bwd) w = std::conj(w);
+          each([&](std::vector<CF>& v) {
+            for (int t = 0; t < active; ++t)
+              for (int jj = 0; jj < NA; ++jj) {
+                const cf y = cf(v[t * NA + jj].re, v[t * NA + jj].im) * (((jj >> bit) & 1) ? std::conj(w) : w);
+                v[t * NA + jj] = CF{y.real(), y.imag()};
+              }
+          });
+        };
+        // a run group, from the table row and the per-sample rows
+        auto group = [&](const EpochRec& E, int row) {
+          const float* co = cp.tco + (int64_t)row * kTabCoefs;
+          const bool scaled = run_form(R) == kFormScaled, twice = scaled && turns_twice(co[kTabLeft]);
+          float tt[kMaxR], ss[kMaxR];
+          for (int j = 0; j < R; ++j) {
+            tt[j] = co[j];
+            ss[j] = co[kTabSine + j];
+          }
+          bool ps_twice = false;
+          const int ps = E.flags & kEpochPs ? E.ps_mask : 0;
+          auto coefs = [&](int at) {
+            double nrm = 1.0;
+            for (int j = 0; j < R; ++j)
+              if ((ps >> j) & 1) {
+                if (E.ref[j] >= 0) oob("shared run in the per-sample mask");
+                tt[j] = coef_row(E.ref[j], sample)[at];
+                ss[j] = coef_row(E.ref[j], sample)[1];
+                nrm *= 1.0 + (double)tt[j] * tt[j];
+              }
+            return nrm;
+          };
+          if (ps) {
+            float sc = (float)(1.0 / std::sqrt(coefs(6)));
+            if (scaled) {
+              ps_twice = turns_twice(sc);
+              if (ps_twice) sc = (float)(1.0 / coefs(7));
+              for (cf& p : ph) p *= sc;
+            }
+          }
+          for (int i = 0; i < 2; ++i)
+            for (int j = 0; j < R; ++j)
+              if (i == 0 || ((ps >> j) & 1 ? ps_twice : twice))
+                each([&](std::vector<CF>& v) { rotate(v, j, L.bwd ? -tt[j] : tt[j], L.bwd ? -ss[j] : ss[j]); });
+        };
+        // the tile through LDS; register contributions from the epoch's record
+        auto exchange = [&](const EpochRec& E, int from, int to) {
+          each([&](std::vector<CF>& v) {
+            std::vector<char> seen(k_amps, 0);
+            for (int t = 0; t < active; ++t)
+              for (int jj = 0; jj < NA; ++jj) {
+                const uint32_t e = (tbase(S.layouts[from].lds_thr, t) ^ reg_index(E.lds_from, jj)) / kLdsElemBytes;
+                if (e >= k_amps || seen[e]) throw std::runtime_error("LDS layout is not a bijection");
+                seen[e] = 1;
+                lds[e] = v[t * NA + jj];
+              }
+            for (int t = 0; t < active; ++t)
+              for (int jj = 0; jj < NA; ++jj) {
+                const uint32_t e = (tbase(S.layouts[to].lds_thr, t) ^ reg_index(E.lds_to, jj)) / kLdsElemBytes;
+                if (e >= k_amps) oob("LDS read");
+                v[t * NA + jj] = lds[e];
+              }
+          });
+        };
+        auto func = [&](const EpochRec& E) {
+          const int ns = pr.n_slots;
+          for (int j = 0; j < R; ++j) {
+            const int slot = E.slot[j];
+            if (slot < 0) continue;   // register bit without a run of this group
+            float fw[3] = {0, 0, 0};
+            for (int w = 0; w < waves; ++w) {
+              float fx = 0, fy = 0, fz = 0;
+              for (int t = w * 64; t < std::min(active, (w + 1) * 64); ++t)
+                for (int jj = 0; jj < NA; ++jj) {
+                  if ((jj >> j) & 1) continue;
+                  CF p0 = a[t * NA + jj], p1 = a[t * NA + (jj | (1 << j))];
+                  CF l0 = l[t * NA + jj], l1 = l[t * NA + (jj | (1 << j))];
+                  fx += l0.re * p1.im - l0.im * p1.re + l1.re * p0.im - l1.im * p0.re;
+                  fy += -(l0.re * p1.re + l0.im * p1.im) + (l1.re * p0.re + l1.im * p0.im);
+                  fz += (l0.re * p0.im - l0.im * p0.re) - (l1.re * p1.im - l1.im * p1.re);
+                }
+              fw[0] += fx;
+              fw[1] += fy;
+              fw[2] += fz;
+            }
+            if (E.flags & kEpochNoX) fw[0] = 0;
+            const int64_t pf = item * 3 * ns + 3 * slot;
+            if (slot >= ns || pf + 3 > (int64_t)L.nb * tiles * 3 * ns) oob("partF");
+            in_ws(L.partF + pf, 12, "partF address");
+            std::memcpy(L.partF + pf, fw, sizeof(fw));
+          }
+        };
+        auto owed = [&](int t, int row) {
+          const float* p = cp.tab + 2 * ((int64_t)row * S.NT + t);
+          return L.bwd ? cf(p[0], -p[1]) : cf(p[0], p[1]);
+        };
+        // consecutive epochs: table row and layout count up (forward) or down (adjoint) by one
+        int at = -1;   // the tile's layout
+        auto epochs = [&](const Op& op) {
+          const int step = L.bwd ? -1 : 1;
+          if (op.b < 1 || op.a < 0 || op.a + op.b > (int)S.epochs.size()) oob("epoch records");
+          if (!same_layout(at, op.e)) throw std::runtime_error("epochs start from another layout");
+          at = op.e;
+          if (L.bwd)
+            for (int t = 0; t < active; ++t) ph[t] *= owed(t, op.c);
+          for (int i = 0; i < op.b; ++i) {
+            const EpochRec& E = S.epochs[op.a + i];
+            const int row = op.c + step * i, to = op.d + step * i;
+            if (row < 0 || row >= (int)S.tabs.size() || to < 0 || to >= (int)S.layouts.size()) oob("epoch row or layout");
+            check_epoch(E, row, at, to, L.bwd);
+            if (!L.bwd) {
+              flush();
+              if (!(E.flags & kEpochStay)) exchange(E, at, to);
+              at = to;
+              for (int t = 0; t < active; ++t) ph[t] = owed(t, row);
+            } else {
+              func(E);
+              group(E, row);
+            }
+            if (L.bwd && (E.flags & kEpochCza)) cza(E.cza, at);
+            if (!L.bwd && (E.flags & kEpochLoop)) diagt(at, E.czg_first, E.czg_loop, E.pev_first, E.pev_loop);
+            if (E.flags & kEpochPhaseA)
+              for (int p = E.pha_first; p < E.pha_first + E.pha_count; ++p) phasea(S.phas[p].regbit, S.phas[p].ref);
+            if (L.bwd && (E.flags & kEpochLoop)) diagt(at, E.czg_first, E.czg_loop, E.pev_first, E.pev_loop);
+            if (!L.bwd && (E.flags & kEpochCza)) cza(E.cza, at);
+            if (!L.bwd) {
+              group(E, row);
+            } else {
+              flush();
+              exchange(E, at, to);
+              at = to;
+              if (i + 1 < op.b)
+                for (int t = 0; t < active; ++t) ph[t] = owed(t, row + step);
+            }
+          }
+        };
         for (int oi = 0; oi < nops; ++oi) {
-          const std::vector<Op> seq = expand_op(S.ops[b0 + oi], L.bwd);
-          for (const Op& op : seq) {
+          const Op& op = S.ops[b0 + oi];
+          // the kernels' programs are straight: tile in, (adjoint: lambda,) epochs and single ops, tile out
+          const bool load = op.kind == OP_INIT0 || op.kind == OP_LOAD;
+          if (load != (oi == 0 || (L.bwd && oi == 1 && op.kind != OP_SEED)) || (op.kind == OP_SEED) != (L.bwd && oi == 1 && !load) ||
+              (op.kind == OP_STORE && oi + 1 != nops))
+            throw std::runtime_error("program is not straight");
           switch (op.kind) {
             case OP_INIT0: {
               const LayoutRec& Ly = S.layouts[op.a];
@@ -315,117 +583,22 @@ struct CpuExec {
                 }
               break;
             }
-            case OP_PERM: {
-              flush();
-              const LayoutRec& F = S.layouts[op.a];
-              const LayoutRec& T = S.layouts[op.b];
-              for (int which = 0; which < (L.bwd ? 2 : 1); ++which) {
-                std::vector<CF>& v = which == 0 ? a : l;
-                std::vector<char> seen(k_amps, 0);
-                for (int t = 0; t < active; ++t)
-                  for (int jj = 0; jj < NA; ++jj) {
-                    uint32_t e = (tbase(F.lds_thr, t) ^ reg_index(F.lds_reg, jj)) / kLdsElemBytes;
-                    if (e >= k_amps || seen[e]) throw std::runtime_error("LDS layout is not a bijection");
-                    seen[e] = 1;
-                    lds[e] = v[t * NA + jj];
-                  }
-                for (int t = 0; t < active; ++t)
-                  for (int jj = 0; jj < NA; ++jj) {
-                    uint32_t e = (tbase(T.lds_thr, t) ^ reg_index(T.lds_reg, jj)) / kLdsElemBytes;
-                    if (e >= k_amps) oob("LDS read");
-                    v[t * NA + jj] = lds[e];
-                  }
-              }
+            case OP_EPOCH:
+              epochs(op);
               break;
-            }
-            case OP_RY:
-            case OP_RYG: {
-              const int m = op.kind == OP_RY ? 1 : op.a;
-              uint32_t seen = 0;
-              for (int e = 0; e < m; ++e) {
-                int j = op.a, ref = op.b;
-                if (op.kind == OP_RYG) {
-                  if (op.b + e >= (int)S.rygs.size()) oob("RYG entry");
-                  j = S.rygs[op.b + e].regbit;
-                  ref = S.rygs[op.b + e].ref;
-                  if (j < 0 || j >= R || ((seen >> j) & 1)) oob("RYG register bit");
-                  seen |= 1u << j;
-                }
-                // rotation by f = b/2 as three shears: tan(f/2) and sin f
-                const float* u = coef_row(ref, sample);
-                const float tt = L.bwd ? -u[6] : u[6], ss = L.bwd ? -u[1] : u[1];
-                for (int which = 0; which < (L.bwd ? 2 : 1); ++which) {
-                  std::vector<CF>& v = which == 0 ? a : l;
-                  for (int t = 0; t < active; ++t)
-                    for (int jj = 0; jj < NA; ++jj) {
-                      if ((jj >> j) & 1) continue;
-                      CF& x0 = v[t * NA + jj];
-                      CF& x1 = v[t * NA + (jj | (1 << j))];
-                      x0.re = std::fma(-tt, x1.re, x0.re);
-                      x0.im = std::fma(-tt, x1.im, x0.im);
-                      x1.re = std::fma(ss, x0.re, x1.re);
-                      x1.im = std::fma(ss, x0.im, x1.im);
-                      x0.re = std::fma(-tt, x1.re, x0.re);
-                      x0.im = std::fma(-tt, x1.im, x0.im);
-                    }
-                }
-              }
-              if (op.kind == OP_RYG && (int)seen != op.c) oob("RYG bit mask");
+            case OP_DIAGT:
+              diagt(op.a, op.b, op.c, op.d, op.e);
               break;
-            }
-            case OP_DIAGT: {
-              const LayoutRec& Ly = S.layouts[op.a];
-              for (int t = 0; t < active; ++t) {
-                const uint32_t xl = tlog | tbase(Ly.log_thr, t);
-                uint32_t par = 0;
-                for (int gi = 0; gi < op.c; ++gi) {
-                  const CzGroup& g = S.czg[op.b + gi];
-                  par ^= xl & (xl >> g.shift) & g.mask;
-                }
-                if (__builtin_popcount(par) & 1) ph[t] = -ph[t];
-                for (int ei = 0; ei < op.e; ++ei) {
-                  const PhaseEv& e = S.pev[op.d + ei];
-                  cf w = event_w(e.ref, sample);
-                  const bool bit = (xl >> e.q) & 1;
-                  if (bit != L.bwd) w = std::conj(w);
-                  ph[t] *= w;
-                }
-              }
+            case OP_CZA:
+              cza(op.a, op.b);
               break;
-            }
-            case OP_CZA: {
-              const CzaRec& cr = S.cza[op.a];
-              const LayoutRec& Ly = S.layouts[op.b];
-              for (int t = 0; t < active; ++t) {
-                const uint32_t xl = tlog | tbase(Ly.log_thr, t);
-                for (int jj = 0; jj < NA; ++jj) {
-                  int sgn = (cr.sr >> jj) & 1;
-                  for (int j = 0; j < R; ++j)
-                    if ((jj >> j) & 1) sgn ^= __builtin_popcount(xl & cr.cmask[j]) & 1;
-                  if (!sgn) continue;
-                  a[t * NA + jj] = CF{-a[t * NA + jj].re, -a[t * NA + jj].im};
-                  if (L.bwd) l[t * NA + jj] = CF{-l[t * NA + jj].re, -l[t * NA + jj].im};
-                }
-              }
+            case OP_PHASEA:
+              if (op.c != S.pev[op.b].ref) oob("phase event");
+              phasea(op.a, op.c);
               break;
-            }
-            case OP_PHASEA: {
-              const PhaseEv& e = S.pev[op.b];
-              cf w = event_w(e.ref, sample);
-              if (L.bwd) w = std::conj(w);
-              for (int which = 0; which < (L.bwd ? 2 : 1); ++which) {
-                std::vector<CF>& v = which == 0 ? a : l;
-                for (int t = 0; t < active; ++t)
-                  for (int jj = 0; jj < NA; ++jj) {
-                    const cf f = ((jj >> op.a) & 1) ? std::conj(w) : w;
-                    cf y = cf(v[t * NA + jj].re, v[t * NA + jj].im) * f;
-                    v[t * NA + jj] = CF{y.real(), y.imag()};
-                  }
-              }
-              break;
-            }
             case OP_EXPECT: {
               if (!L.do_expect) break;
+              flush();
               const LayoutRec& Ly = S.layouts[op.a];
               for (int w = 0; w < waves; ++w)
                 for (int k = 0; k < K; ++k) {
@@ -459,77 +632,70 @@ struct CpuExec {
                 }
               break;
             }
-            case OP_FUNC: {
-              const int ns = pr.n_slots;
-              for (int e = 0; e < op.a; ++e) {
-                const FuncEntry& fe = S.funcs[op.b + e];
-                if (fe.slot < 0) continue;   // register bit without a run of this group
-                const int j = fe.regbit;
-                float fw[3] = {0, 0, 0};
-                for (int w = 0; w < waves; ++w) {
-                  float fx = 0, fy = 0, fz = 0;
-                  for (int t = w * 64; t < std::min(active, (w + 1) * 64); ++t)
-                    for (int jj = 0; jj < NA; ++jj) {
-                      if ((jj >> j) & 1) continue;
-                      CF p0 = a[t * NA + jj], p1 = a[t * NA + (jj | (1 << j))];
-                      CF l0 = l[t * NA + jj], l1 = l[t * NA + (jj | (1 << j))];
-                      fx += l0.re * p1.im - l0.im * p1.re + l1.re * p0.im - l1.im * p0.re;
-                      fy += -(l0.re * p1.re + l0.im * p1.im) + (l1.re * p0.re + l1.im * p0.im);
-                      fz += (l0.re * p0.im - l0.im * p0.re) - (l1.re * p1.im - l1.im * p1.re);
-                    }
-                  fw[0] += fx;
-                  fw[1] += fy;
-                  fw[2] += fz;
-                }
-                const int64_t pf = item * 3 * ns + 3 * fe.slot;
-                if (fe.slot < 0 || fe.slot >= ns || pf + 3 > (int64_t)L.nb * tiles * 3 * ns) oob("partF");
-                float* dst = L.partF + pf;
-                in_ws(dst, 12, "partF address");
-                dst[0] = op.d ? 0.f : fw[0];   // (kEpochNoX: the pass kernels leave it out)
-                dst[1] = fw[1];
-                dst[2] = fw[2];
-              }
-              break;
-            }
             default:
               throw std::runtime_error("unknown op");
           }
-          }
+          if (load) at = op.a;
         }
       }
     }
   }
 
-  // An epoch op as the sub-ops of its epochs in execution order; any other op
-  // as itself.
-  std::vector<Op> expand_op(const Op& o, bool bwd) const {
-    if (o.kind != OP_EPOCH) return {o};
+  // Layouts that hold the tile alike (the layout of a pass's store is a copy with other
+  // memory bits).
+  bool same_layout(int i, int j) const {
+    const LayoutRec &a = c.S.layouts[i], &b = c.S.layouts[j];
+    return std::memcmp(a.lds_reg, b.lds_reg, sizeof(a.lds_reg)) == 0 && std::memcmp(a.lds_thr, b.lds_thr, sizeof(a.lds_thr)) == 0 &&
+           std::memcmp(a.log_reg, b.log_reg, sizeof(a.log_reg)) == 0 && std::memcmp(a.log_thr, b.log_thr, sizeof(a.log_thr)) == 0;
+  }
+
+  // The kernels take an epoch's row and layouts from counters and its items from flags and
+  // first counts; the planner's own fields must say the same.
+  void check_epoch(const EpochRec& E, int row, int at, int to, bool bwd) const {
     const Schedule& S = c.S;
-    std::vector<Op> out;
-    if (o.b < 1 || o.a < 0 || o.a + o.b > (int)S.epochs.size()) oob("epoch records");
-    for (int ei = o.a; ei < o.a + o.b; ++ei) {
-      const EpochRec& e = S.epochs[ei];
-      std::vector<Op> perm, diag, pha, cza, ry, func;
-      if (e.perm_from >= 0) perm.push_back({OP_PERM, e.perm_from, e.perm_to, 0, 0, 0, 0, 0});
-      if (e.diag_layout >= 0)
-        diag.push_back({OP_DIAGT, e.diag_layout, e.czg_first, e.czg_count, e.pev_first, e.pev_count, 0, 0});
-      for (int i = 0; i < e.pha_count; ++i) {
-        if (e.pha_first + i >= (int)S.phas.size()) oob("epoch PHASEA entry");
-        pha.push_back({OP_PHASEA, S.phas[e.pha_first + i].regbit, S.phas[e.pha_first + i].pev, 0, 0, 0, 0, 0});
-      }
-      if (e.cza >= 0) cza.push_back({OP_CZA, e.cza, e.cza_layout, 0, 0, 0, 0, 0});
-      if (e.ry_b != 0) {
-        int cnt = 0;
-        for (int j = 0; j < 32; ++j) cnt += (e.ry_b >> j) & 1;
-        ry.push_back({OP_RYG, cnt, e.ry_a, e.ry_b, 0, 0, 0, 0});
-      }
-      if (e.func_count > 0)
-        func.push_back({OP_FUNC, e.func_count, e.func_first, 0, e.flags & kEpochNoX, 0, 0, 0});
-      auto add = [&](const std::vector<Op>& v) { out.insert(out.end(), v.begin(), v.end()); };
-      if (!bwd) { add(perm); add(diag); add(pha); add(cza); add(ry); }
-      else { add(func); add(ry); add(cza); add(pha); add(diag); add(perm); }
+    auto need = [](bool ok, const char* what) {
+      if (!ok) throw std::runtime_error(std::string("epoch record: ") + what);
+    };
+    const bool stay = (E.flags & kEpochStay) != 0;
+    const int layout = bwd ? at : to;   // of the group and the diagonal items
+    const TabRec& T = S.tabs[row];
+    need(E.tab == row && E.perm_to == to && (stay ? E.perm_from == -1 && at == to : E.perm_from == at), "layouts");
+    need(same_layout(T.layout, layout), "layout of the row");
+    need(E.diag_layout < 0 || same_layout(E.diag_layout, layout), "layout of the diagonal items");
+    need((E.cza >= 0) == ((E.flags & kEpochCza) != 0) && (E.cza < 0 || same_layout(E.cza_layout, layout)), "CZ signs");
+    need((E.pha_count > 0) == ((E.flags & kEpochPhaseA) != 0), "register phases");
+    need(E.pha_first + E.pha_count <= (int)S.phas.size(), "register phase range");
+    need(((E.czg_loop | E.pev_loop) != 0) == ((E.flags & kEpochLoop) != 0), "loop items");
+    // loop items and the row's items are the DIAGT items
+    need(T.czg_first == E.czg_first + E.czg_loop && T.czg_count == E.czg_count - E.czg_loop, "CZ groups of the row");
+    need(T.tev_count == E.pev_count - E.pev_loop, "events of the row");
+    std::vector<int> cor;
+    for (int i = 0; i < E.pev_count; ++i) {
+      const PhaseEv& p = S.pev[E.pev_first + i];
+      if (i < E.pev_loop) continue;
+      const TabEvent& e = S.tevs[T.tev_first + i - E.pev_loop];
+      need(p.ref >= 0 && e.q == p.q && e.prev_ref == S.events[p.ref].prev_ref &&
+               e.next_ref == S.events[p.ref].next_ref, "event of the row");
     }
-    return out;
+    for (int i = 0; i < E.pha_count; ++i) cor.push_back(S.phas[E.pha_first + i].ref);
+    for (int i = 0; i < E.pev_loop; ++i) cor.push_back(S.pev[E.pev_first + i].ref);
+    cor.erase(std::remove_if(cor.begin(), cor.end(), [](int r) { return r < 0; }), cor.end());
+    std::vector<int> of_row(S.tcor.begin() + T.cor_first, S.tcor.begin() + T.cor_first + T.cor_count);
+    std::sort(cor.begin(), cor.end());   // (the adjoint applies them in reverse)
+    std::sort(of_row.begin(), of_row.end());
+    need(cor == of_row, "corrected events of the row");
+    // run group: bits, refs, per-sample mask
+    int n = 0;
+    for (int j = 0; j < S.R; ++j) {
+      const bool run = (E.ry_b >> j) & 1;
+      const int ref = run ? S.rygs[E.ry_a + n].ref : 0;
+      need(!run || S.rygs[E.ry_a + n].regbit == j, "register bit of a run");
+      n += run;
+      need(E.ref[j] == ref && ((E.ps_mask >> j) & 1) == (ref < 0), "run of a register bit");
+      need(T.ref[j] == (run && ref >= 0 ? ref : INT32_MIN), "run of the row");
+      need(!bwd || (E.slot[j] >= 0) == run, "slot of a run");
+    }
+    need((E.ps_mask != 0) == ((E.flags & kEpochPs) != 0), "per-sample runs");
   }
 
   void reduce_E(int nb, int sample0, const float* partE, float* E) {
@@ -543,8 +709,9 @@ struct CpuExec {
   }
 
   // grad_i = 1/2 Im<lambda| K_i P_i K_i^dag |psi> at the cut after the run,
-  // K_i = product of the run's gates after gate i.
-  void run_grads(int r, int sample, double fx, double fy, double fz, float* Grow, bool zyz) const {
+  // K_i = product of the run's gates after gate i: put(gate, half its generator)
+  template <class Put>
+  void generators(int r, int sample, bool zyz, Put put) const {
     const RunRec& rr = c.S.runs[r];
     const cd z = zyz ? split(run_matrix(r, sample)).z : cd(1, 0);
     M2 Kc;
@@ -553,31 +720,83 @@ struct CpuExec {
       const GateRec& g = c.S.gates[c.S.run_gates[rr.gate_begin + i]];
       M2 G = mul(mul(Kc, pauli(g.kind)), dag(Kc));
       const cd g10 = z * G.m[2];
-      double gr = 0.5 * (g10.real() * fx + g10.imag() * fy + G.m[0].real() * fz);
-      Grow[g.out_idx] = (float)gr;
+      put(g.out_idx, 0.5 * g10.real(), 0.5 * g10.imag(), 0.5 * G.m[0].real());
       Kc = mul(Kc, rot(g.kind, angle(g, sample)));
     }
   }
+  void run_grads(int r, int sample, const double* f, float* Grow, bool zyz) const {
+    generators(r, sample, zyz, [&](int g, double nx, double ny, double nz) {
+      Grow[g] = (float)(nx * f[0] + ny * f[1] + nz * f[2]);
+    });
+  }
 
+  double* fsum = nullptr;   // column sums of the functionals, in chunks of rows
+  int64_t fsum_stride(int seg) const {
+    return 3ll * (c.S.pass_run_begin[c.seg_begin[seg + 1]] - c.S.pass_run_begin[c.seg_begin[seg]]);
+  }
+  void sum_functionals(int seg, int nb, const float* partF) {
+    const int64_t rows = (int64_t)nb * c.tiles;
+    for (int p = c.seg_begin[seg]; p < c.seg_begin[seg + 1]; ++p) {
+      const int ncol = 3 * c.S.passes[p].n_slots;
+      const float* base = partF + (int64_t)nb * c.partF_off[p];
+      for (int k = 0; k < c.fsum_chunks; ++k)
+        for (int col = 0; col < ncol; ++col) {
+          double acc = 0;
+          for (int64_t r = rows * k / c.fsum_chunks; r < rows * (k + 1) / c.fsum_chunks; ++r) acc += base[r * ncol + col];
+          double* out = fsum + k * fsum_stride(seg) +
+                        3ll * (c.S.pass_run_begin[p] - c.S.pass_run_begin[c.seg_begin[seg]]) + col;
+          in_ws(out, 8, "functional sum");
+          *out = acc;
+        }
+    }
+  }
   void assemble(int seg, int nb, int sample0, const float*, const float*, const float* partF, float* Gr) {
-    for (int s = 0; s < nb; ++s)
-      for (int i = c.seg_run_begin[seg]; i < c.seg_run_begin[seg + 1]; ++i) {
-        const int r = c.seg_runs[i];
-        const RunRec& rr = c.S.runs[r];
-        const int ns = c.S.passes[rr.pass].n_slots;
-        const float* base = partF + (int64_t)nb * c.partF_off[rr.pass];
+    sum_functionals(seg, nb, partF);
+    assemble_sums(seg, nb, sample0, partF, Gr);
+  }
+  // shared runs, summed over the micro-batch, into row 0; per-sample runs into their rows
+  void assemble_sums(int seg, int nb, int sample0, const float* partF, float* Gr) {
+    const Schedule& S = c.S;
+    for (int p = c.seg_begin[seg]; p < c.seg_begin[seg + 1]; ++p) {
+      const int ns = S.passes[p].n_slots, rb = S.pass_run_begin[p], rb0 = S.pass_run_begin[c.seg_begin[seg]];
+      const float* base = partF + (int64_t)nb * c.partF_off[p];
+      for (int slot = 0; slot < ns; ++slot) {
+        const RunRec& rr = S.runs[S.pass_runs[rb + slot]];
+        if (rr.coef < 0) continue;
         double f[3] = {0, 0, 0};
-        for (int it = 0; it < c.tiles; ++it)
-          for (int P = 0; P < 3; ++P) f[P] += base[(((int64_t)s * c.tiles) + it) * 3 * ns + 3 * rr.slot + P];
-        run_grads(r, sample0 + s, f[0], f[1], f[2], Gr + (int64_t)s * c.n_angle, true);
+        for (int P = 0; P < 3; ++P) {
+          if (c.fsum_chunks > 0)
+            for (int k = 0; k < c.fsum_chunks; ++k) f[P] += fsum[k * fsum_stride(seg) + 3ll * (rb - rb0 + slot) + P];
+          else
+            for (int64_t r = 0; r < (int64_t)nb * c.tiles; ++r) f[P] += base[r * 3 * ns + 3 * slot + P];
+        }
+        for (int i = 0; i < rr.gate_count; ++i) {
+          const int g = S.gates[S.run_gates[rr.gate_begin + i]].out_idx;
+          const double* v = cp.gvec + 3ll * g;
+          Gr[g] = (float)(v[0] * f[0] + v[1] * f[1] + v[2] * f[2]);
+        }
       }
+      const auto e = std::find(c.ps_pass.begin(), c.ps_pass.end(), p);
+      if (e == c.ps_pass.end()) continue;
+      const int64_t i = e - c.ps_pass.begin();
+      for (int s = 0; s < nb; ++s)
+        for (int q = c.ps_begin[i]; q < c.ps_begin[i + 1]; ++q) {
+          const int r = c.ps_runs[q];
+          double f[3] = {0, 0, 0};
+          for (int it = 0; it < c.tiles; ++it)
+            for (int P = 0; P < 3; ++P) f[P] += base[((int64_t)s * c.tiles + it) * 3 * ns + 3 * S.runs[r].slot + P];
+          run_grads(r, sample0 + s, f, Gr + (int64_t)s * c.n_angle, true);
+        }
+    }
   }
 
   void reduce_grads(int nb, int sample0, const float* Gr, float* dtheta, float* dx, bool accumulate) {
     for (int p = 0; p < c.C.P; ++p) {
       double acc = 0;
-      for (int s = 0; s < nb; ++s)
-        for (int i = c.th_ref_begin[p]; i < c.th_ref_begin[p + 1]; ++i) acc += Gr[(int64_t)s * c.n_angle + c.th_refs[i]];
+      for (int i = c.th_ref_begin[p]; i < c.th_ref_begin[p + 1]; ++i) {
+        const int g = c.th_refs[i];
+        for (int s = 0; s < (c.gate_ps[g] ? nb : 1); ++s) acc += Gr[(int64_t)s * c.n_angle + g];
+      }
       dtheta[p] = accumulate ? dtheta[p] + (float)acc : (float)acc;
     }
     if (dx)
@@ -711,7 +930,7 @@ struct CpuExec {
         double f[3] = {0, 0, 0};
         for (int b = 0; b < c.pg_blocks; ++b)
           for (int P = 0; P < 3; ++P) f[P] += partF[(((int64_t)s * c.pg_chunk + slot) * c.pg_blocks + b) * 3 + P];
-        run_grads(r, sample0 + s, f[0], f[1], f[2], Gr + (int64_t)s * c.n_angle, false);
+        run_grads(r, sample0 + s, f, Gr + (int64_t)s * c.n_angle, false);
       }
   }
 };
@@ -753,6 +972,7 @@ int qfc_run_psi0(const qf_circuit_desc* desc, int32_t batch, const qf_tuning* tu
       ex.in_lo = (const char*)psi0;
       ex.in_hi = ex.in_lo + pc.state_bytes * batch;
     }
+    ex.fsum = at<double>(base, pc.off_fsum);
     run_forward(pc, ex, theta, x, E, base, psi0);
     if (dE) run_backward(pc, ex, theta, x, dE, dtheta, dx, base, psi0);
     return 0;
@@ -894,6 +1114,7 @@ int qfc_batch_run(const qf_circuit_desc* const* descs, const int32_t* samples, i
       ex.emplace_back(new CpuExec(*cores[i]));
       ex.back()->ws_lo = base + off[i];
       ex.back()->ws_hi = base + off[i] + cores[i]->ws_bytes;
+      ex.back()->fsum = at<double>(base + off[i], cores[i]->off_fsum);
     }
     auto rb = [&](auto p) { return p ? reinterpret_cast<decltype(p)>(base + reinterpret_cast<uintptr_t>(p)) : p; };
     auto replay = [&](const Program& P) {
@@ -918,12 +1139,11 @@ int qfc_batch_run(const qf_circuit_desc* const* descs, const int32_t* samples, i
           const int c = j.circ;
           switch (j.kind) {
             case SJ_COEF: e.coef(theta[c], x[c], base + off[c]); break;
-            case SJ_FSUM: break;    // the emulated assembly adds the functionals itself
-            case SJ_EVENT: break;   // the emulated coefficient step also fills the phase events
+            case SJ_FSUM: e.sum_functionals(j.u.fs.p0 / cores[c]->ckpt, j.u.fs.nb, rb(j.u.fs.partF)); break;
+            case SJ_EVENT: break;   // the emulated coefficient step also fills events, tables and generators
             case SJ_REDUCE_E: e.reduce_E(j.u.re.nb, j.u.re.sample0, rb(j.u.re.partE), E[c]); break;
             case SJ_ASSEMBLE:
-              e.assemble(j.u.as.p0 / cores[c]->ckpt, j.u.as.nb, j.u.as.sample0, theta[c], x[c], rb(j.u.as.partF),
-                         rb(j.u.as.Gr));
+              e.assemble_sums(j.u.as.p0 / cores[c]->ckpt, j.u.as.nb, j.u.as.sample0, rb(j.u.as.partF), rb(j.u.as.Gr));
               break;
             case SJ_REDUCE_G:
               e.reduce_grads(j.u.rg.nb, j.u.rg.sample0, rb(j.u.rg.Gr), dtheta[c], dx ? dx[c] : nullptr,

@@ -15,6 +15,13 @@ namespace qf {
 enum RunForm : int { kFormMatrix = 0, kFormShear = 1, kFormScaled = 2 };
 inline int run_form(int R) { return R <= 4 ? kFormScaled : kFormShear; }
 
+// Least cosine of a scaled rotation: t = tan f stays below 2^25 and the growth of four
+// below 2^100.  The cosine moves by less than half an ulp of 1, the rounding of the
+// rotated amplitudes.
+constexpr double kMinCos = 1.0 / (1 << 25);
+// Rows of the epoch tables whose scales' roundings carry over to the next (see table_body).
+constexpr int kCarryRows = 8;
+
 // Coefficient, reduction and gradient arguments carry the real type of the call:
 // float on the fused and per-gate paths, double on the complex128 validation path.
 template <class Real>

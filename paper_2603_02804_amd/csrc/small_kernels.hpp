@@ -126,11 +126,6 @@ __device__ inline D2 run_matrix(const Tabs& T, const RunRec& rr, const Real* the
   return U;
 }
 
-// Least cosine of a scaled rotation: t = tan f stays below 2^25 and the growth of four
-// below 2^100.  The cosine moves by less than half an ulp of 1, the rounding of the
-// rotated amplitudes.
-constexpr double kMinCos = 1.0 / (1 << 25);
-
 // Run coefficients, f = b/2 of the RZ(a) RY(b) RZ(c) split.
 //   kFormShear   [cos f, sin f, u, v, tan(f/2), 0]
 //   kFormScaled  [cos f, sin f, u, v, t = tan f, tan(f/2)]
@@ -240,7 +235,6 @@ __device__ inline double row_scale(const EventArgs& a, const TabRec* r) {
 // (1/sqrt(2) of a CNOT's quarter turn: -1.7e-8): every row also owes what that of the rows
 // before it left, from the last multiple of kCarryRows on.  A workgroup's rows lie in one
 // such window; its first threads form the window's scales.
-constexpr int kCarryRows = 8;
 __device__ inline void table_body(const EventArgs& a, int blk, int thread, double* scales) {
   const long long idx = (long long)blk * kSmallThreads + thread;
   const int row = (int)(idx / a.NT), t = (int)(idx - (long long)row * a.NT);
