@@ -239,12 +239,13 @@ def bench_hea(args, dev) -> int:
         "flops_per_launch": flops_bwd / max(1, n_bwd), "bytes_per_launch": bytes_bwd / max(1, n_bwd),
         "hbm_gbs": round(bytes_bwd / bwd_s / 1e9, 1) if bwd_s > 0 else 0.0,
     }
-    # the forward pass kernel beside it (16 algorithmic flops per run-amplitude, 4 executed)
+    # the forward pass kernel beside it (16 algorithmic flops per run-amplitude; executed: 4, or 6 as shears
+    # with five register qubits)
     fwd_flops = info.fwd_flops_per_sample * B * args.steps
     fwd_tf = fwd_flops / fwd_s / 1e12 if fwd_s > 0 else 0.0
     fwd_roof = {"kernel": f"k_pass<{info.reg_qubits},{info.threads},false> (fused forward pass)",
                 "achieved": round(fwd_tf, 2), "frac": round(fwd_tf / PEAK_FP32_TFLOPS, 4),
-                "executed_tflops": round(fwd_tf * 4 / 16, 2), "launches": n_fwd,
+                "executed_tflops": round(fwd_tf * (4 if info.reg_qubits <= 4 else 6) / 16, 2), "launches": n_fwd,
                 "avg_launch_ms": round(prof.ms[0] / max(1, n_fwd), 4),
                 "hbm_gbs": round(info.fwd_bytes_per_sample * B * args.steps / fwd_s / 1e9, 1) if fwd_s > 0 else 0.0}
     step_bytes = (info.fwd_bytes_per_sample + info.bwd_bytes_per_sample) * B

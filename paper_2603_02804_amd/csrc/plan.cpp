@@ -380,6 +380,7 @@ static void fuse_epochs(Schedule* Sp) {
   };
   auto emit = [&](EpochRec* e, int step) {
     complete(e, step > 0 || e->perm_from < 0 ? e->perm_to : e->perm_from);
+    if (step < 0 && (e->flags & kEpochNoX)) S.n_no_x += __builtin_popcount(e->ry_b);
     const EpochRec* p = S.epochs.empty() ? nullptr : &S.epochs.back();
     if ((int)out.size() > cur_begin && out.back().kind == OP_EPOCH &&
         out.back().a + out.back().b == (int)S.epochs.size() && e->tab == p->tab + step &&

@@ -83,6 +83,7 @@ struct Schedule {
   // per-sample op counts over all forward passes
   int64_t n_perm = 0, n_u2 = 0, n_cz = 0;
   int64_t n_groups = 0;               // run groups (register epochs)
+  int64_t n_no_x = 0;                 // runs in adjoint epochs without X functionals
   int64_t n_diag_thread = 0, n_diag_amp = 0;   // diagonal items folded per thread / applied per amplitude
 };
 

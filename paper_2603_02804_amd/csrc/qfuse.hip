@@ -842,7 +842,7 @@ qf_status qf_plan_get_info(const qf_plan* p, qf_plan_info* info) {
   // flops).  The kernels execute fewer: the run is a real RY between diagonal phases,
   // applied without its cosine (4 flops per amplitude; 6 as shears with five register
   // qubits), so the adjoint pass executes 2 x 4 + 12 (three functionals) = 20 flops per
-  // amplitude and run.
+  // amplitude and run, 16 in the epochs without X functionals (four register qubits only).
   const double runs = (double)S.n_u2;
   info->fwd_flops_per_sample = runs * 16 * A;
   double rec_runs = 0;
@@ -854,7 +854,7 @@ qf_status qf_plan_get_info(const qf_plan* p, qf_plan_info* info) {
   info->bwd_pass_flops_per_sample = runs * 48 * A;
   info->bwd_flops_per_sample = info->bwd_pass_flops_per_sample + rec_runs * 16 * A +
                                (c.store ? 0 : info->fwd_flops_per_sample);
-  info->exec_bwd_pass_flops_per_sample = runs * (S.R <= 4 ? 20 : 24) * A;
+  info->exec_bwd_pass_flops_per_sample = (runs * (S.R <= 4 ? 20 : 24) - (S.R == 4 ? 4.0 * S.n_no_x : 0.0)) * A;
   info->bwd_pass_launches = (int64_t)c.P * ((c.B + c.mb - 1) / c.mb);
   return QF_OK;
 }
