@@ -50,23 +50,6 @@ __device__ __forceinline__ CzGroup ld_czg(const CzGroup* p) {
   return g;
 }
 
-// Register-bit dispatch: expands STMT with the compile-time bit J == j.
-#define QF_WITH_BIT(R, j, STMT)                      \
-  switch (j) {                                       \
-    case 0: { constexpr int J = 0; STMT; } break;    \
-    case 1: if constexpr (R > 1) { constexpr int J = 1; STMT; } break; \
-    case 2: if constexpr (R > 2) { constexpr int J = 2; STMT; } break; \
-    case 3: if constexpr (R > 3) { constexpr int J = 3; STMT; } break; \
-    case 4: if constexpr (R > 4) { constexpr int J = 4; STMT; } break; \
-    default: break;                                  \
-  }
-
-// log2 of the threads of a workgroup (a tile with fewer thread bits leaves lanes idle)
-template <int NT>
-struct ThreadBitsOf {
-  static constexpr int value = NT <= 64 ? 6 : NT <= 128 ? 7 : 8;
-};
-
 // Per-register-bit contributions of a layout, loaded once per op (uniform).
 template <int R>
 struct RegBits {
@@ -93,10 +76,6 @@ __device__ __forceinline__ void cmul_in(float2& a, float2 b) {
   const float t2 = a.y * b.x;
   a.y = fmaf(a.x, b.y, t2);
   a.x = fmaf(a.x, b.x, -t1);
-}
-
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-  return make_float2(fmaf(a.x, b.x, -a.y * b.y), fmaf(a.x, b.y, a.y * b.x));
 }
 
 // Real rotation [[cos f, -sin f], [sin f, cos f]] on the pairs along register
@@ -151,14 +130,6 @@ __device__ __forceinline__ void apply_group(float2 (&a)[1 << R], const float (&t
     else apply_ry<R, J>(a, t[J], s[J]);
     apply_group<R, J + 1>(a, t, s);
   }
-}
-
-// Diagonal phase on register bit J: w where the bit is 0, conj(w) where it is 1.
-template <int R, int J>
-__device__ __forceinline__ void apply_phase_reg(float2 (&a)[1 << R], float2 w) {
-  const float2 wc = make_float2(w.x, -w.y);
-#pragma unroll
-  for (int i = 0; i < (1 << R); ++i) cmul_in(a[i], (i & (1 << J)) ? wc : w);
 }
 
 // Im<l|X_q|a>, Im<l|Y_q|a>, Im<l|Z_q|a> over the pairs along register bit J.

@@ -62,7 +62,6 @@ struct PlanCore {
   std::vector<int32_t> coef_runs_sh, coef_runs_ps;
   std::vector<int64_t> partF_off;     // per pass, floats, from the start of its segment
   int64_t partF_seg_floats = 0;       // per sample, largest segment
-  std::vector<int32_t> seg_runs, seg_run_begin;
   std::vector<int32_t> th_ref_begin, th_refs, in_ref_begin, in_refs;
   // per-gate baseline
   int pg_chunk = 0;                   // rotation gates per partial-sum chunk
@@ -195,19 +194,6 @@ inline qf_status build_plan_core(const Circuit& C, int B, const Tuning& T, PlanC
     }
     c.partF_seg_floats = std::max(c.partF_seg_floats, acc);
   }
-  // runs per segment
-  c.seg_run_begin.assign(c.n_seg + 1, 0);
-  std::vector<std::vector<int32_t>> per_seg(c.n_seg);
-  for (size_t r = 0; r < S.runs.size(); ++r) {
-    int s = S.runs[r].pass / c.ckpt;
-    per_seg[s].push_back((int)r);
-  }
-  for (int s = 0; s < c.n_seg; ++s) {
-    c.seg_run_begin[s] = (int)c.seg_runs.size();
-    c.seg_runs.insert(c.seg_runs.end(), per_seg[s].begin(), per_seg[s].end());
-  }
-  c.seg_run_begin[c.n_seg] = (int)c.seg_runs.size();
-
   size_t off = 0;
   const int nck = c.store ? B : c.mb;
   c.off_coef_sh = off; off = align_up(off + sizeof(float) * 8 * std::max(1, S.n_coef_shared));

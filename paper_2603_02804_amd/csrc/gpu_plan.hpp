@@ -58,40 +58,36 @@ inline qf_status upload_plan(const PlanCore& c, DevPlan* d, std::string* msg) {
   push_table(blob, o, c.S.ops);          // 0
   push_table(blob, o, c.S.layouts);      // 1
   push_table(blob, o, c.S.czg);          // 2
-  push_table(blob, o, c.S.funcs);        // 3
-  push_table(blob, o, c.S.passes);       // 4
-  push_table(blob, o, zm);               // 5
-  push_table(blob, o, c.S.runs);         // 6
-  push_table(blob, o, c.S.run_gates);    // 7
-  push_table(blob, o, c.S.gates);        // 8
-  push_table(blob, o, c.coef_runs_sh);   // 9
-  push_table(blob, o, c.coef_runs_ps);   // 10
-  push_table(blob, o, c.partF_off);      // 11
-  push_table(blob, o, c.seg_runs);       // 12
-  push_table(blob, o, c.seg_run_begin);  // 13
-  push_table(blob, o, c.th_ref_begin);   // 14
+  push_table(blob, o, c.S.passes);       // 3
+  push_table(blob, o, zm);               // 4
+  push_table(blob, o, c.S.runs);         // 5
+  push_table(blob, o, c.S.run_gates);    // 6
+  push_table(blob, o, c.S.gates);        // 7
+  push_table(blob, o, c.coef_runs_sh);   // 8
+  push_table(blob, o, c.coef_runs_ps);   // 9
+  push_table(blob, o, c.partF_off);      // 10
+  push_table(blob, o, c.th_ref_begin);   // 11
   std::vector<int32_t> th_refs;
   for (int g : c.th_refs) th_refs.push_back(c.gate_ps[g] ? g : -1 - g);
-  push_table(blob, o, th_refs);          // 15
-  push_table(blob, o, c.in_ref_begin);   // 16
-  push_table(blob, o, c.in_refs);        // 17
-  push_table(blob, o, c.S.pev);          // 18
-  push_table(blob, o, c.S.cza);          // 19
-  push_table(blob, o, c.S.events);       // 20
-  push_table(blob, o, c.S.pass_run_begin);  // 21
-  push_table(blob, o, c.S.pass_runs);    // 22
-  push_table(blob, o, c.S.rygs);         // 23
-  push_table(blob, o, c.S.epochs);       // 24
-  push_table(blob, o, c.S.phas);         // 25
-  push_table(blob, o, pauli_table(c));   // 26
-  push_table(blob, o, c.C.consts);       // 27
-  push_table(blob, o, thread_base_table(c.S));   // 28
-  push_table(blob, o, c.S.tabs);         // 29
-  push_table(blob, o, c.ps_pass);        // 30
-  push_table(blob, o, c.ps_begin);       // 31
-  push_table(blob, o, c.ps_runs);        // 32
-  push_table(blob, o, c.S.tevs);         // 33
-  push_table(blob, o, c.S.tcor);         // 34
+  push_table(blob, o, th_refs);          // 12
+  push_table(blob, o, c.in_ref_begin);   // 13
+  push_table(blob, o, c.in_refs);        // 14
+  push_table(blob, o, c.S.pev);          // 15
+  push_table(blob, o, c.S.cza);          // 16
+  push_table(blob, o, c.S.events);       // 17
+  push_table(blob, o, c.S.pass_run_begin);  // 18
+  push_table(blob, o, c.S.pass_runs);    // 19
+  push_table(blob, o, c.S.epochs);       // 20
+  push_table(blob, o, c.S.phas);         // 21
+  push_table(blob, o, pauli_table(c));   // 22
+  push_table(blob, o, c.C.consts);       // 23
+  push_table(blob, o, thread_base_table(c.S));   // 24
+  push_table(blob, o, c.S.tabs);         // 25
+  push_table(blob, o, c.ps_pass);        // 26
+  push_table(blob, o, c.ps_begin);       // 27
+  push_table(blob, o, c.ps_runs);        // 28
+  push_table(blob, o, c.S.tevs);         // 29
+  push_table(blob, o, c.S.tcor);         // 30
   d->bytes = blob.size();
   if (hipMalloc(&d->blob, d->bytes) != hipSuccess) {
     if (msg) *msg = "hipMalloc of plan tables failed";
@@ -106,40 +102,36 @@ inline qf_status upload_plan(const PlanCore& c, DevPlan* d, std::string* msg) {
   p.ops = (const Op*)(b + o[0]);
   p.layouts = (const LayoutRec*)(b + o[1]);
   p.czg = (const CzGroup*)(b + o[2]);
-  p.funcs = (const FuncEntry*)(b + o[3]);
-  p.passes = (const PassRec*)(b + o[4]);
-  p.zmask = (const uint32_t*)(b + o[5]);
+  p.passes = (const PassRec*)(b + o[3]);
+  p.zmask = (const uint32_t*)(b + o[4]);
   Tabs& t = p.tabs;
-  t.runs = (const RunRec*)(b + o[6]);
-  t.run_gates = (const int32_t*)(b + o[7]);
-  t.gates = (const GateRec*)(b + o[8]);
-  t.coef_runs_sh = (const int32_t*)(b + o[9]);
-  t.coef_runs_ps = (const int32_t*)(b + o[10]);
+  t.runs = (const RunRec*)(b + o[5]);
+  t.run_gates = (const int32_t*)(b + o[6]);
+  t.gates = (const GateRec*)(b + o[7]);
+  t.coef_runs_sh = (const int32_t*)(b + o[8]);
+  t.coef_runs_ps = (const int32_t*)(b + o[9]);
   t.passes = p.passes;
-  t.partF_off = (const int64_t*)(b + o[11]);
-  t.seg_runs = (const int32_t*)(b + o[12]);
-  t.seg_run_begin = (const int32_t*)(b + o[13]);
-  t.th_ref_begin = (const int32_t*)(b + o[14]);
-  t.th_refs = (const int32_t*)(b + o[15]);
-  t.in_ref_begin = (const int32_t*)(b + o[16]);
-  t.in_refs = (const int32_t*)(b + o[17]);
-  p.pev = (const PhaseEv*)(b + o[18]);
-  p.cza = (const CzaRec*)(b + o[19]);
-  t.events = (const EventRec*)(b + o[20]);
-  t.pass_run_begin = (const int32_t*)(b + o[21]);
-  t.pass_runs = (const int32_t*)(b + o[22]);
-  t.ps_pass = (const int32_t*)(b + o[30]);
-  t.ps_begin = (const int32_t*)(b + o[31]);
-  t.ps_runs = (const int32_t*)(b + o[32]);
-  p.rygs = (const RygEntry*)(b + o[23]);
-  p.epochs = (const EpochRec*)(b + o[24]);
-  p.phas = (const PhaEntry*)(b + o[25]);
-  p.pauli = (const PauliRec*)(b + o[26]);
-  t.consts = (const double*)(b + o[27]);
-  p.tbases = (const ThrBase*)(b + o[28]);
-  p.trecs = (const TabRec*)(b + o[29]);
-  p.tevs = (const TabEvent*)(b + o[33]);
-  p.tcor = (const int32_t*)(b + o[34]);
+  t.partF_off = (const int64_t*)(b + o[10]);
+  t.th_ref_begin = (const int32_t*)(b + o[11]);
+  t.th_refs = (const int32_t*)(b + o[12]);
+  t.in_ref_begin = (const int32_t*)(b + o[13]);
+  t.in_refs = (const int32_t*)(b + o[14]);
+  p.pev = (const PhaseEv*)(b + o[15]);
+  p.cza = (const CzaRec*)(b + o[16]);
+  t.events = (const EventRec*)(b + o[17]);
+  t.pass_run_begin = (const int32_t*)(b + o[18]);
+  t.pass_runs = (const int32_t*)(b + o[19]);
+  t.ps_pass = (const int32_t*)(b + o[26]);
+  t.ps_begin = (const int32_t*)(b + o[27]);
+  t.ps_runs = (const int32_t*)(b + o[28]);
+  p.epochs = (const EpochRec*)(b + o[20]);
+  p.phas = (const PhaEntry*)(b + o[21]);
+  p.pauli = (const PauliRec*)(b + o[22]);
+  t.consts = (const double*)(b + o[23]);
+  p.tbases = (const ThrBase*)(b + o[24]);
+  p.trecs = (const TabRec*)(b + o[25]);
+  p.tevs = (const TabEvent*)(b + o[29]);
+  p.tcor = (const int32_t*)(b + o[30]);
   return QF_OK;
 }
 

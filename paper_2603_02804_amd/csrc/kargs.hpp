@@ -20,8 +20,6 @@ struct Tabs {
   const int32_t* coef_runs_ps;
   const PassRec* passes;
   const int64_t* partF_off;
-  const int32_t* seg_runs;
-  const int32_t* seg_run_begin;
   const int32_t* th_ref_begin;
   const int32_t* th_refs;       // gate g of a per-sample run, or -1 - g of a shared one
   const int32_t* in_ref_begin;
@@ -38,8 +36,6 @@ struct PlanPtrs {
   const Op* ops = nullptr;
   const LayoutRec* layouts = nullptr;
   const CzGroup* czg = nullptr;
-  const FuncEntry* funcs = nullptr;
-  const RygEntry* rygs = nullptr;
   const EpochRec* epochs = nullptr;
   const PhaEntry* phas = nullptr;
   const PassRec* passes = nullptr;

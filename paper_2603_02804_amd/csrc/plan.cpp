@@ -295,7 +295,6 @@ static void fuse_epochs(Schedule* Sp) {
     return e;
   };
   auto take_ry = [&](const Op& o, EpochRec* e) {
-    e->ry_kind = 2;
     if (o.kind == OP_RY) {   // a single run becomes a group of one
       e->ry_a = (int)S.rygs.size();
       e->ry_b = 1 << o.a;
@@ -436,7 +435,7 @@ static void fuse_epochs(Schedule* Sp) {
       EpochRec e = blank();
       int j = i;
       if (k == OP_FUNC) {
-        e.func_count = S.ops[j].a; e.func_first = S.ops[j].b; e.func_full = S.ops[j].c;
+        e.func_count = S.ops[j].a; e.func_first = S.ops[j].b;
         ++j;
       }
       take_ry(S.ops[j++], &e);

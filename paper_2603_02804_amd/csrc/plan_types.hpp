@@ -170,9 +170,9 @@ struct EpochRec {
   int32_t cza, cza_layout;                             // CZA (-1: none)
   int32_t perm_from, perm_to;                          // PERM (from -1: none, to: the layout)
   int32_t tab;                                         // row of the epoch tables (TabRec)
-  int32_t ry_kind, ry_a, ry_b;                         // run group: first RygEntry a, bit mask b (0: none)
-  int32_t func_count, func_first, func_full;           // FUNC (backward; func_full unused)
-  int32_t pad[6];
+  int32_t ry_a, ry_b;                                  // run group: first RygEntry a, bit mask b
+  int32_t func_count, func_first;                      // FUNC (backward)
+  int32_t pad[8];
 };
 static_assert(sizeof(EpochRec) % 64 == 0, "epoch records are whole cache lines");
 

@@ -1087,7 +1087,7 @@ int qfc_batch_run(const qf_circuit_desc* const* descs, const int32_t* samples, i
       cores.push_back(&c);
       PlanPtrs pp;   // host copies of the tables: only their addresses enter the jobs
       pp.ops = c.S.ops.data(); pp.layouts = c.S.layouts.data(); pp.czg = c.S.czg.data();
-      pp.funcs = c.S.funcs.data(); pp.rygs = c.S.rygs.data(); pp.epochs = c.S.epochs.data(); pp.phas = c.S.phas.data(); pp.passes = c.S.passes.data(); pp.pev = c.S.pev.data(); pp.cza = c.S.cza.data();
+      pp.epochs = c.S.epochs.data(); pp.phas = c.S.phas.data(); pp.passes = c.S.passes.data(); pp.pev = c.S.pev.data(); pp.cza = c.S.cza.data();
       ptrs.push_back(pp);
     }
     std::vector<uint64_t> off;
