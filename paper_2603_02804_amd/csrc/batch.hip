@@ -316,8 +316,7 @@ qf_status qf_batch_create(const qf_circuit* const* circuits, const int32_t* samp
   }
   hipGetDevice(&b->device);
   b->samples.assign(samples, samples + n_circuits);
-  // merged launches step every circuit pass by pass, so by default no
-  // end-of-pass epoch waits for the next pass (fewer passes, fewer steps)
+  // (zero fields take the batch defaults, see batch_plan_tuning)
   qf_tuning bt;
   std::memset(&bt, 0, sizeof(bt));
   bt.store_ckpt = -1;
