@@ -52,7 +52,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_coef(const CoefArgsT<Real> a)
 }
 
 __global__ __launch_bounds__(kSmallThreads) void k_event_coef(const EventArgs a) {
-  __shared__ double red[kCarryRows];
+  __shared__ double red[2 * kCarryRows];
   event_body(a, blockIdx.x, threadIdx.x, red);
 }
 

@@ -196,23 +196,17 @@ __device__ inline float2 shared_event(const double* dsh, const EventRec& e) {
   return make_float2((float)wr, (float)wi);
 }
 
-// The scale that a row's shared runs owe as rotations by f, and whether they turn twice
-// (rounded as the pass kernel compares it).
-__device__ inline double row_left(const EventArgs& a, const TabRec* r, bool* twice) {
-  double left = 1.0;
+// The scale that a row of the epoch tables owes: of its shared runs' rotations, and of
+// the rounded norms of the shared phases that the pass kernel applies itself.  left: the
+// product of their cosines, rounded as the pass kernel compares it.
+__device__ inline bool turns_twice(double left) { return (float)left < 1.f / kMaxGrowth; }
+__device__ inline double row_scale(const EventArgs& a, const TabRec* r, double* left) {
+  double scale = 1.0;
 #pragma unroll
   for (int j = 0; j < kMaxR; ++j)
-    if (r->ref[j] != INT32_MIN) left *= a.dsh[kDshRow * (long long)r->ref[j] + 4];
-  *twice = (float)left < 1.f / kMaxGrowth;
-  return left;
-}
-
-// The scale that a row of the epoch tables owes: of its shared runs' rotations, and of
-// the rounded norms of the shared phases that the pass kernel applies itself.
-__device__ inline double row_scale(const EventArgs& a, const TabRec* r) {
-  bool twice;
-  double scale = row_left(a, r, &twice);
-  if (twice) {   // 1/(1 + h^2) of h = tan(f/2) each
+    if (r->ref[j] != INT32_MIN) scale *= a.dsh[kDshRow * (long long)r->ref[j] + 4];
+  *left = scale;
+  if (turns_twice(scale)) {   // 1/(1 + h^2) of h = tan(f/2) each
     double halves = 1.0;
     for (int j = 0; j < kMaxR; ++j)
       if (r->ref[j] != INT32_MIN) {
@@ -234,12 +228,14 @@ __device__ inline double row_scale(const EventArgs& a, const TabRec* r) {
 // scale's own rounding would change all amplitudes alike, with the same sign in many rows
 // (1/sqrt(2) of a CNOT's quarter turn: -1.7e-8): every row also owes what that of the rows
 // before it left, from the last multiple of kCarryRows on.  A workgroup's rows lie in one
-// such window; its first threads form the window's scales.
+// such window; its first threads form the window's scales and, behind them in scales, the
+// products of cosines.
 __device__ inline void table_body(const EventArgs& a, int blk, int thread, double* scales) {
   const long long idx = (long long)blk * kSmallThreads + thread;
   const int row = (int)(idx / a.NT), t = (int)(idx - (long long)row * a.NT);
   const int window = (int)((long long)blk * kSmallThreads / a.NT) / kCarryRows * kCarryRows;
-  if (thread < kCarryRows && window + thread < a.n_tab) scales[thread] = row_scale(a, a.trecs + window + thread);
+  if (thread < kCarryRows && window + thread < a.n_tab)
+    scales[thread] = row_scale(a, a.trecs + window + thread, scales + kCarryRows + thread);
   __syncthreads();
   if (row >= a.n_tab) return;
   const TabRec* r = a.trecs + row;
@@ -291,9 +287,8 @@ __device__ inline void table_body(const EventArgs& a, int blk, int thread, doubl
   if (t < kTabCoefs) {
     const int j = t & 7;
     const bool present = j < kMaxR && r->ref[j] != INT32_MIN;
-    bool twice;
-    const double left = row_left(a, r, &twice);
-    float v = present ? a.csh[8 * (long long)r->ref[j] + (t >= kTabSine ? 1 : twice ? 7 : 6)] : 0.f;
+    const double left = scales[kCarryRows + row - window];
+    float v = present ? a.csh[8 * (long long)r->ref[j] + (t >= kTabSine ? 1 : turns_twice(left) ? 7 : 6)] : 0.f;
     if (t == kTabLeft && a.form == kFormScaled) v = (float)left;
     a.tco[(long long)row * kTabCoefs + t] = v;
   }
